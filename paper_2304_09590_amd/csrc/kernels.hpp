@@ -167,6 +167,7 @@ struct GemmArgs {
     // [s*kchunk, (s+1)*kchunk) and writes C + s * c_split (EPI_STORE only)
     int ksplit, kchunk;
     int64_t c_split;
+    int z0;  // gemm_kernel: first batch index of this launch (a batch dimension beyond the grid's limit)
     // epilogue
     const float* bias;      // EPI_FWD: bias[n] (+ z * bias_z)
     int64_t bias_z;
@@ -715,7 +716,7 @@ __global__ __launch_bounds__(256) void gemm_kernel(GemmArgs g) {
     __shared__ GemmLds<BF, A_KC, B_KC> lds;
     int bx, by, bz;
     gemm_tile(bx, by, bz);
-    gemm_body<BF, TA, TB, A_KC, B_KC, EPI, TO, WPRE>(g, bx, by, bz, lds);
+    gemm_body<BF, TA, TB, A_KC, B_KC, EPI, TO, WPRE>(g, bx, by, bz + g.z0 * g.ksplit, lds);
 }
 
 // Two independent weight updates of the bf16 mini-batch plan (two wide layers, samples along
@@ -2869,6 +2870,10 @@ struct PsgdPArgs {
     long spin_limit;
 };
 
+// row stride of a persistent launch's Gram blocks [T][psgd_gs(T)]: conflict-free matrix-operand
+// reads, and a block is a whole number of the 1 KiB pieces that wave_copy_to_lds moves
+__device__ __host__ constexpr int psgd_gs(int T) { return T == 64 ? 68 : 40; }
+
 constexpr int MAX_IB = 13;  // input blocks of 16 per wave of a tile (4 waves x 13 x 16 >= 784)
 
 // Wave-level bounded wait (no workgroup barrier inside): every lane polls the same flag.
@@ -3216,6 +3221,12 @@ __device__ inline void lds_publish(int* f, int v) {
 //                  Wave 2 also publishes each finished block's d1 for the tile workgroups
 //                  and announces finished chunks to them; wave 3 early in each chunk loads
 //                  the next chunk's Gram blocks and labels into LDS.
+// Chunk length T: 64 steps for up to 128 neurons (HW = 64 NH), 32 for up to 384.  LDS (Pl, hist)
+// and the fold waves' accumulators grow as HW T, and so does the matrix work of a fold, so twice
+// the neurons with half the steps cost the same of each; a chunk of 32 steps still takes the live
+// wave far longer (24 us) than the tiles need for their next Q.  Bound: the live wave's chain of
+// dependent steps, 0.52 us a step for 128 neurons, 0.74 us for 256 and 1.0 us for 384.  784-256-10,
+// K = 4, 8,000 rows: 20.2 ms in psgd_chunk_kernel launches (9.9 us a step) -> 1.5 ms.
 // Counters (LDS): d1done (steps whose d1 is in hist), cdone (rows whose cpre is ready),
 // rdy (per folding wave: leading blocks whose rows of Pl are final), gready (chunks whose
 // Gram blocks and labels are in LDS), pubd (blocks whose d1 has been copied out of hist),
@@ -3224,12 +3235,13 @@ template <int T, int NH, int A1, int A2, int LS, int OC>
 __device__ __attribute__((always_inline)) inline void psgd_rec(const PsgdPArgs& a, int k, float* smem) {
     constexpr int HW = 64 * NH;     // neurons covered by the live wave
     constexpr int TS = T + 4;       // row stride of the error history ([neuron][step in chunk])
-    constexpr int GS = T + 4;       // row stride of the Gram blocks (conflict-free MFMA operand reads)
+    constexpr int GS = psgd_gs(T);  // row stride of the Gram blocks
+    constexpr int LT = T == 64 ? 6 : 5;  // log2(T)
     constexpr int BS = 8;           // steps per fold block
     constexpr int NLIVE = 5;        // latest errors whose terms the live wave adds itself (<= BS; the
                                     // live step below is written out for five)
     constexpr int NB = T / BS;      // blocks per chunk
-    static_assert(T == 64, "chunks of 64 steps");
+    static_assert(T == 64 || T == 32, "chunks of 64 or 32 steps");
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int H = a.H, K = a.k_rep;
     const float lr = a.lr;
@@ -3239,8 +3251,8 @@ __device__ __attribute__((always_inline)) inline void psgd_rec(const PsgdPArgs& 
     float* Gin = hist + HW * TS;        // [2][T][GS] Gram blocks within a chunk, by parity
     float* GX = Gin + 2 * T * GS;       // [T][GS]    a chunk (rows) against the previous one
     float* cpre = GX + T * GS;          // [8][HW]    window corrections by row mod 8
-    int* yb = (int*)(cpre + 8 * HW);    // [2][T]     labels by chunk parity
-    int* lf = yb + 2 * T;
+    int* yb = (int*)(cpre + 8 * HW);    // [2][64]    labels by chunk parity
+    int* lf = yb + 2 * 64;
     int* d1done = lf;
     int* cdone = lf + 1;
     int* rdy = lf + 2;     // [2]: one counter per folding wave
@@ -3315,7 +3327,7 @@ __device__ __attribute__((always_inline)) inline void psgd_rec(const PsgdPArgs& 
         // the in-block offsets are compile-time, and the rotation of the recent errors is a
         // register renaming.
         for (int r0 = 0; r0 < nsteps; r0 += BS) {
-            const int c = r0 >> 6, t0 = r0 & (T - 1);
+            const int c = r0 >> LT, t0 = r0 & (T - 1);
             const int tc = chunk_len(c);
 #pragma unroll
         for (int i = 0; i < BS; ++i) {
@@ -3336,7 +3348,7 @@ __device__ __attribute__((always_inline)) inline void psgd_rec(const PsgdPArgs& 
             // operands of the step's end, read up front (unconditional loads from valid
             // addresses, so every path leaves the same LDS reads in flight)
             const int rn = more ? r + 1 : r;
-            const int cn = rn >> 6, tn = rn & (T - 1);
+            const int cn = rn >> LT, tn = rn & (T - 1);
             float cp[NH], pnx[NH];
 #pragma unroll
             for (int j = 0; j < NH; ++j) pnx[j] = Pl[(lane + 64 * j) * TS + tn];
@@ -3354,7 +3366,7 @@ __device__ __attribute__((always_inline)) inline void psgd_rec(const PsgdPArgs& 
             const float g3v = (cross || t < 3) ? gx[tp3] : gin[tp3];
             const int tp4 = (t + T - 4) & (T - 1);     // position of step r-4 in its chunk
             const float g4v = (cross || t < 4) ? gx[tp4] : gin[tp4];
-            const int labn = yb[(cn & 1) * T + tn];
+            const int labn = yb[(cn & 1) * 64 + tn];
 
             float a1[NH], na[NH];
 #pragma unroll
@@ -3460,7 +3472,7 @@ __device__ __attribute__((always_inline)) inline void psgd_rec(const PsgdPArgs& 
         // cpre[q] = sum over s in [BS(B-1), q-1-NLIVE] of d1_s (x_s . x_q)
         for (int r = 0; r + 1 < nsteps; ++r) {
             const int q = r + 1;
-            const int cq = q >> 6, tq = q & (T - 1), B = q / BS;
+            const int cq = q >> LT, tq = q & (T - 1), B = q / BS;
             // the live wave has finished step q-1-NLIVE: d1 up to there is in hist.  The slot
             // (q & 7) last held the correction of row q-8, read in step q-9: free.
             lds_wait_geq(d1done, r + 1 - NLIVE, lab, gabort, a.spin_limit, false);
@@ -3475,7 +3487,7 @@ __device__ __attribute__((always_inline)) inline void psgd_rec(const PsgdPArgs& 
             for (int part = 0; part < 2; ++part) {
                 const int sb = BS * (B - 1 + part);  // first step of the group
                 if (sb < lo || sb > hi) continue;
-                const int cs = sb >> 6, ts = sb & (T - 1);
+                const int cs = sb >> LT, ts = sb & (T - 1);
                 // Gram row of q against the group's steps: same chunk -> G_cq, else GX_cq
                 const float* gq = (cs == cq ? grow_in(cq) : GX) + tq * GS + ts;
                 const int last = hi - sb;  // highest offset included (>= 0)
@@ -3591,7 +3603,7 @@ __device__ __attribute__((always_inline)) inline void psgd_rec(const PsgdPArgs& 
                     {
                         const int rr = min(lane, tcn - 1);
                         __builtin_amdgcn_global_load_lds(a.y + xs + (int64_t)cn * T + rr,
-                                                         (lds_void*)(yb + (cn & 1) * T), 4, 0, 0);
+                                                         (lds_void*)(yb + (cn & 1) * 64), 4, 0, 0);
                     }
                     wait_vm_all();
                     ++loaded;

@@ -8,9 +8,10 @@
 //
 // Training plans:
 //  * per-sample SGD of a one-hidden-layer fp32 network (B = 1, L = 2, hidden <= 1024,
-//    outputs <= 16): chunked plan -- Gram matrices of each chunk of T samples, then per
-//    chunk P = W1 x_t (GEMM), the T sequential steps (psgd_chunk_kernel), and the rank-T
-//    update of W1 (GEMM).
+//    outputs <= 16): hidden <= 384, one persistent launch per epoch and group of CNs
+//    (psgd_persistent_kernel); wider, the chunked plan -- Gram matrices of each chunk of T
+//    samples, then per chunk P = W1 x_t (GEMM), the T sequential steps (psgd_chunk_kernel), and
+//    the rank-T update of W1 (GEMM).
 //  * everything else: mini-batch plan -- per batch step, forward GEMMs with fused bias and
 //    activation, output layer with fused output error, hidden errors (GEMM with fused
 //    phi'), and weight-gradient GEMMs with the SGD update (and bias update) fused into the
@@ -634,25 +635,38 @@ pnn_status minibatch_step(pnn_net* n, const float* X, const int32_t* Y, int64_t 
 // ---------------------------------------------------------------------------------------
 // chunked per-sample plan
 
-constexpr int PT = 64;            // chunk length of the persistent per-sample plan
+// chunk length of the persistent per-sample plan for H hidden neurons.  Up to 128 neurons, 64
+// steps; up to 384, 32 steps: the sequential workgroup keeps the input sums and errors of a whole
+// chunk for every neuron in LDS, and the fold waves two chunks of input sums in registers, so
+// twice the neurons take half the steps.
+int psgd_chunk_len(int H) { return H <= 128 ? 64 : 32; }
 constexpr long SPIN_LIMIT = 1L << 22;
 
-// kernel instance: hidden neurons per lane of the live wave (1: <= 64, 2: <= 128) x
+// kernel instance: hidden neurons per lane of the live wave (1: <= 64, 2: <= 128, 4: <= 256,
+// 6: <= 384) x
 // activation specialisation x 16-row sub-tiles per tile workgroup (1, or 2 when more CNs must
 // fit the chip)
+template <int T, int NH, int RT>
+const void* persistent_fn_of(const pnn_net* n) {
+    return n->pspecial ? (const void*)psgd_persistent_kernel<T, NH, ACT_SIGMOID, ACT_SIGMOID, LOSS_MSE, 10, RT>
+                       : (const void*)psgd_persistent_kernel<T, NH, -1, -1, -1, 16, RT>;
+}
 template <int RT>
 const void* persistent_fn_rt(const pnn_net* n) {
-    const bool narrow = n->sizes[1] <= 64;
-    if (n->pspecial)
-        return narrow ? (const void*)psgd_persistent_kernel<PT, 1, ACT_SIGMOID, ACT_SIGMOID, LOSS_MSE, 10, RT>
-                      : (const void*)psgd_persistent_kernel<PT, 2, ACT_SIGMOID, ACT_SIGMOID, LOSS_MSE, 10, RT>;
-    return narrow ? (const void*)psgd_persistent_kernel<PT, 1, -1, -1, -1, 16, RT>
-                  : (const void*)psgd_persistent_kernel<PT, 2, -1, -1, -1, 16, RT>;
+    const int H = n->sizes[1];
+    if (H <= 64) return persistent_fn_of<64, 1, RT>(n);
+    if (H <= 128) return persistent_fn_of<64, 2, RT>(n);
+    if (H <= 256) return persistent_fn_of<32, 4, RT>(n);
+    return persistent_fn_of<32, 6, RT>(n);
 }
 const void* persistent_fn(const pnn_net* n) { return n->prt == 2 ? persistent_fn_rt<2>(n) : persistent_fn_rt<1>(n); }
 
 // width of the live wave's neuron set (input-sum rows are padded to it)
-int live_width(int H) { return H <= 64 ? 64 : 128; }
+constexpr int PSGD_MAX_H = 384;
+int live_width(int H) { return H <= 64 ? 64 : H <= 128 ? 128 : H <= 256 ? 256 : PSGD_MAX_H; }
+
+// floats of the Gram blocks of an epoch with slices of nmax rows, in the launches per chunk
+size_t psgd_gram_elems(int K, int64_t nmax, int T) { return (size_t)K * ((nmax + T - 1) / T) * T * T; }
 
 // after a persistent launch: its abort flag is read by the next call that consumes the CNs
 pnn_status note_persistent_launch(pnn_net* n, hipStream_t s) {
@@ -665,6 +679,7 @@ pnn_status note_persistent_launch(pnn_net* n, hipStream_t s) {
 pnn_status psgd_persistent_epoch(pnn_net* n, const float* X, const int32_t* Y, int64_t N, hipStream_t s) {
     const int K = n->cfg.replicas, H = n->sizes[1], In = n->sizes[0];
     const int64_t nmax = shard_len(N, K, 0);
+    const int PT = psgd_chunk_len(H);
     const int nch = (int)((nmax + PT - 1) / PT);
     auto grow = [&](float** buf, size_t* have, size_t need) -> pnn_status {
         if (need <= *have) return PNN_OK;
@@ -675,9 +690,18 @@ pnn_status psgd_persistent_epoch(pnn_net* n, const float* X, const int32_t* Y, i
         *have = need;
         return PNN_OK;
     };
-    constexpr int GS = PT + 4;  // padded Gram row stride (matches the kernel's LDS layout)
-    TRY(grow(&n->gram, &n->gram_elems, (size_t)K * nch * PT * GS));
+    const int GS = psgd_gs(PT);  // padded Gram row stride (the kernel's LDS layout)
+    TRY(grow(&n->gram, &n->gram_elems, std::max((size_t)K * nch * PT * GS, n->T > 0 ? psgd_gram_elems(K, nmax, n->T) : 0)));
     TRY(grow(&n->gramx, &n->gramx_elems, (size_t)K * std::max(nch - 1, 1) * PT * GS));
+    // (products z = CN * chunks + chunk, in launches of at most 65,535, the grid's limit)
+    auto gram_products = [&](GemmArgs& g, int64_t total) -> pnn_status {
+        for (int64_t z0 = 0; z0 < total; z0 += 65535) {
+            g.z0 = (int)z0;
+            const int Z = (int)std::min<int64_t>(65535, total - z0);
+            TRY((run_gemm<false, float, float, true, true, EPI_STORE, float>(n, s, g, Z, "psgd_gram")));
+        }
+        return PNN_OK;
+    };
     {
         // G_c[t][s] = x_t . x_s within every chunk
         GemmArgs g = gemm_base(n, PT, PT, In, N, 0, PT, 3);
@@ -685,7 +709,7 @@ pnn_status psgd_persistent_epoch(pnn_net* n, const float* X, const int32_t* Y, i
         g.b = opnd(X, 0, In, 1);
         g.zdiv = nch; g.r0_step = PT;
         g.c = n->gram; g.c_z = (int64_t)PT * GS; g.c_ld = GS;
-        TRY((run_gemm<false, float, float, true, true, EPI_STORE, float>(n, s, g, K * nch, "psgd_gram")));
+        TRY(gram_products(g, (int64_t)K * nch));
     }
     if (nch > 1) {
         // GX_c[t][s] = x_t . x_s, t in chunk c, s in chunk c-1 (always full), c >= 1
@@ -694,7 +718,7 @@ pnn_status psgd_persistent_epoch(pnn_net* n, const float* X, const int32_t* Y, i
         g.b = opnd(X, 0, In, 1, -PT);
         g.zdiv = nch - 1; g.r0_step = PT;
         g.c = n->gramx; g.c_z = (int64_t)PT * GS; g.c_ld = GS;
-        TRY((run_gemm<false, float, float, true, true, EPI_STORE, float>(n, s, g, K * (nch - 1), "psgd_gram")));
+        TRY(gram_products(g, (int64_t)K * (nch - 1)));
     }
     {
         // (the abort slot flags[3K] is sticky: a launch after an abort ends at once)
@@ -797,12 +821,25 @@ pnn_status mbp_epoch(pnn_net* n, const float* X, const int32_t* Y, int64_t N, hi
     return note_persistent_launch(n, s);
 }
 
+// is the stream recording a graph?
+bool capturing(hipStream_t s) {
+    hipStreamCaptureStatus st = hipStreamCaptureStatusNone;
+    if (hipStreamIsCapturing(s, &st) != hipSuccess) {
+        (void)hipGetLastError();
+        return false;
+    }
+    return st == hipStreamCaptureStatusActive;
+}
+
 pnn_status psgd_epoch(pnn_net* n, const float* X, const int32_t* Y, int64_t N, hipStream_t s) {
-    if (n->persistent) return psgd_persistent_epoch(n, X, Y, N, s);
+    // (above 128 neurons an epoch recorded into a graph takes the launches per chunk, whose
+    // workspaces those nets keep: a persistent launch is cooperative and its time-out is read
+    // from the host afterwards)
+    if (n->persistent && !(n->T > 0 && capturing(s))) return psgd_persistent_epoch(n, X, Y, N, s);
     const int K = n->cfg.replicas, T = n->T, H = n->sizes[1], In = n->sizes[0];
     const int64_t nmax = shard_len(N, K, 0);
     const int nch = (int)((nmax + T - 1) / T);
-    const size_t need = (size_t)K * nch * T * T;
+    const size_t need = psgd_gram_elems(K, nmax, T);
     if (need > n->gram_elems) {
         if (n->gram) (void)hipFree(n->gram);
         n->gram = nullptr;
@@ -917,8 +954,10 @@ bool aligned16(const void* p) { return ((uintptr_t)p & 15) == 0; }
 // parameters unspecified.  Every call that consumes the CNs reads the flag of the last such
 // launch first: `wait` waits for that launch to end; without it the flag is read only if the
 // launch has already ended (a later launch of the same kernel ends at once on a set flag).
-pnn_status check_abort(pnn_net* n, bool wait) {
-    if (!n->abort_pending) return PNN_OK;
+// (Not while the stream `s` records a graph, which allows neither the wait nor the copy: the
+// flag then stays for the next call outside it.)
+pnn_status check_abort(pnn_net* n, bool wait, hipStream_t s) {
+    if (!n->abort_pending || (s && capturing(s))) return PNN_OK;
     if (!wait) {
         const hipError_t q = hipEventQuery(n->abort_ev);
         if (q == hipErrorNotReady) return PNN_OK;
@@ -1049,7 +1088,7 @@ pnn_status pnn_init(const pnn_config* cfg, const float* theta0_host, void* hip_s
         int cus = 0;
         if (hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, n->device) != hipSuccess) cus = 0;
         const int H = n->sizes[1], In = n->sizes[0], O = n->sizes[2];
-        const int HW = live_width(H);
+        const int HW = live_width(H), PT = psgd_chunk_len(H);
         // tile workgroups of 16 rows of W1 (rt = 1) or 32 (rt = 2); the CNs go in groups whose
         // workgroups fit the CUs, one launch each.  Of the two, the one with the least estimated
         // time: launches x the relative time of a step (1 with 16-row tiles, 1.8 with 32-row
@@ -1066,16 +1105,16 @@ pnn_status pnn_init(const pnn_config* cfg, const float* theta0_host, void* hip_s
         }
         const int nrb = (H + 16 * rt - 1) / (16 * rt);
         n->prt = rt;
-        // input sums [HW][T+4], errors [HW][T+4], Gram blocks 3 x [T][T+4], window
-        // corrections [8][HW], labels [2][T], 12 counters
+        // input sums [HW][T+4], errors [HW][T+4], Gram blocks 3 x [T][psgd_gs(T)], window
+        // corrections [8][HW], labels [2][64], 12 counters
         const size_t rec_smem =
-            (size_t)(2 * HW * (PT + 4) + 3 * PT * (PT + 4) + 8 * HW + 2 * PT + 12) * sizeof(float);
+            (size_t)(2 * HW * (PT + 4) + 3 * PT * psgd_gs(PT) + 8 * HW + 2 * 64 + 12) * sizeof(float);
         const size_t tile_smem = (size_t)4 * (PT / 16) * rt * 64 * 4 * sizeof(float);
         n->psmem = std::max(rec_smem, tile_smem);
         n->pspecial = n->act[0] == PNN_SIGMOID && n->act[1] == PNN_SIGMOID && cfg->loss == PNN_LOSS_MSE && O == 10;
         const void* fn = persistent_fn(n);
         int per_cu = 0;
-        bool fits = H <= 128 && In <= 4 * MAX_IB * 16 && kg >= 1;
+        bool fits = H <= PSGD_MAX_H && In <= 4 * MAX_IB * 16 && kg >= 1;
         if (fits && hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)n->psmem) != hipSuccess)
             fits = false;
         if (fits && hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, fn, 256, n->psmem) != hipSuccess) fits = false;
@@ -1090,20 +1129,24 @@ pnn_status pnn_init(const pnn_config* cfg, const float* theta0_host, void* hip_s
             // padding neurons and rows of the input sums are never written by the kernel: zero them
             if (hipMemset(n->qbuf, 0, sizeof(float) * qn) != hipSuccess)
                 return bail(fail(n, PNN_EHIP, "hipMemset of the input-sum buffer failed"));
-            if ((st = dev_alloc(n, &n->d1, (size_t)2 * K * PT * H)) != PNN_OK) return bail(st);
             if ((st = dev_alloc(n, &n->flags, (size_t)(3 * K + 1))) != PNN_OK) return bail(st);
         }
+        if (!fits || H > 128) {
+            // launches per chunk: where the persistent kernel does not fit, and above 128 neurons
+            // beside it, for epochs that are recorded into a graph
+            n->T = 128;
+            while (n->T > 16 && (int64_t)n->T * H > 16384) n->T >>= 1;
+        }
+        // errors of a chunk (two chunks in the persistent kernel)
+        const size_t dn = (size_t)K * std::max(fits ? 2 * PT : 0, n->T) * H;
+        if ((st = dev_alloc(n, &n->d1, dn)) != PNN_OK) return bail(st);
     }
-    if (n->psgd && !n->persistent) {
-        const int H = n->sizes[1];
-        int T = 128;
-        while (T > 16 && (int64_t)T * H > 16384) T >>= 1;
-        n->T = T;
+    if (n->psgd && n->T > 0) {
+        const int H = n->sizes[1], T = n->T;
         // split the 784-long contraction of P so that every CN's P uses several CUs
         n->kchunk = (int)round_up((n->sizes[0] + 7) / 8, 16);
         n->ksplit = (n->sizes[0] + n->kchunk - 1) / n->kchunk;
         if ((st = dev_alloc(n, &n->ppart, (size_t)n->ksplit * K * T * H)) != PNN_OK) return bail(st);
-        if ((st = dev_alloc(n, &n->d1, (size_t)K * T * H)) != PNN_OK) return bail(st);
         const size_t smem = (size_t)(2 * T * H + 2 * 16 * MAX_OUT) * sizeof(float);
         hipError_t e = hipSuccess;
         switch (T) {
@@ -1233,8 +1276,8 @@ pnn_status pnn_train_epoch(pnn_net* n, const float* x_dev, const int32_t* y_dev,
     if (!x_dev || !y_dev) return fail(n, PNN_EINVAL, "x_dev / y_dev is NULL");
     if (!aligned16(x_dev)) return fail(n, PNN_EINVAL, "x_dev is not 16-byte aligned");
     if (N < n->cfg.replicas) return fail(n, PNN_ESHAPE, "N = %lld < K = %d leaves a slice empty", (long long)N, n->cfg.replicas);
-    TRY(check_abort(n, false));
     hipStream_t s = (hipStream_t)hip_stream;
+    TRY(check_abort(n, false, s));
     if (!n->fx3) TRY(settle(n, s));
     if (n->psgd) return psgd_epoch(n, x_dev, y_dev, N, s);
     if (n->mbp) return mbp_epoch(n, x_dev, y_dev, N, s);
@@ -1296,7 +1339,7 @@ static pnn_status launch_merge(pnn_net* n, int32_t broadcast, const double* w_de
 
 pnn_status pnn_merge(pnn_net* n, int32_t broadcast, void* hip_stream) {
     TRY(usable(n));
-    TRY(check_abort(n, true));
+    TRY(check_abort(n, true, (hipStream_t)hip_stream));
     return launch_merge(n, broadcast, nullptr, (double)n->cfg.replicas, (hipStream_t)hip_stream);
 }
 
@@ -1311,7 +1354,7 @@ pnn_status pnn_merge_weighted(pnn_net* n, const double* weights_host, int32_t br
         ws += v;
     }
     if (!(ws > 0.0) || !std::isfinite(ws)) return fail(n, PNN_EINVAL, "the weights sum to %g (must be positive)", ws);
-    TRY(check_abort(n, true));
+    TRY(check_abort(n, true, (hipStream_t)hip_stream));
     hipStream_t s = (hipStream_t)hip_stream;
     // the weights travel with the launch's stream order (the copy waits for earlier work)
     HIP_TRY(n, hipMemcpyAsync(n->d_mw, weights_host, sizeof(double) * K, hipMemcpyHostToDevice, s));
@@ -1441,7 +1484,7 @@ pnn_status pnn_infer(pnn_net* n, int32_t which, const float* x_dev, int64_t nrow
     }
     if (!x_dev || !pred_dev) return fail(n, PNN_EINVAL, "x_dev / pred_dev is NULL");
     if (!aligned16(x_dev)) return fail(n, PNN_EINVAL, "x_dev is not 16-byte aligned");
-    TRY(check_abort(n, true));
+    TRY(check_abort(n, true, (hipStream_t)hip_stream));
     hipStream_t s = (hipStream_t)hip_stream;
     if (which >= 0) TRY(settle(n, s));
     const bool count = correct_host && y_dev;
@@ -1468,7 +1511,7 @@ pnn_status pnn_eval(pnn_net* n, int32_t which, const float* x_dev, const int32_t
     }
     if (!x_dev || !y_dev) return fail(n, PNN_EINVAL, "x_dev / y_dev is NULL");
     if (!aligned16(x_dev)) return fail(n, PNN_EINVAL, "x_dev is not 16-byte aligned");
-    TRY(check_abort(n, true));
+    TRY(check_abort(n, true, (hipStream_t)hip_stream));
     hipStream_t s = (hipStream_t)hip_stream;
     if (cost_host && nrows > n->cost_rows) {
         HIP_TRY(n, hipStreamSynchronize(s));
@@ -1504,7 +1547,7 @@ pnn_status pnn_eval_noalloc(pnn_net* n, int32_t which, const float* x_dev, const
     if (need > (int64_t)SCRATCH_BYTES)
         return fail(n, PNN_ESHAPE, "evaluating %lld rows needs %lld bytes of workspace; the fixed workspace has %lld",
                     (long long)nrows, (long long)need, (long long)SCRATCH_BYTES);
-    TRY(check_abort(n, true));
+    TRY(check_abort(n, true, (hipStream_t)hip_stream));
     hipStream_t s = (hipStream_t)hip_stream;
     unsigned long long* correct = (unsigned long long*)base;
     double* cost_sum = (double*)(base + 8);
@@ -1523,7 +1566,7 @@ pnn_status pnn_eval_noalloc(pnn_net* n, int32_t which, const float* x_dev, const
 
 const char* pnn_plan(const pnn_net* n) {
     if (!n) return "";
-    if (n->psgd) return n->persistent ? "per-sample persistent" : "per-sample chunked";
+    if (n->psgd) return n->persistent && n->T == 0 ? "per-sample persistent" : "per-sample chunked";
     return n->mbp ? "mini-batch persistent" : n->fx3 ? "mini-batch fused last layer" : "mini-batch";
 }
 
@@ -1532,7 +1575,7 @@ pnn_status pnn_get_params(pnn_net* n, int32_t which, float* host_out) {
     if (!host_out) return fail(n, PNN_EINVAL, "host_out is NULL");
     if (which < -1 || which >= n->cfg.replicas) return fail(n, PNN_EINVAL, "which = %d out of range", which);
     HIP_TRY(n, hipDeviceSynchronize());
-    TRY(check_abort(n, true));
+    TRY(check_abort(n, true, nullptr));
     if (which >= 0) {
         TRY(settle(n, nullptr));
         HIP_TRY(n, hipDeviceSynchronize());
@@ -1549,7 +1592,7 @@ pnn_status pnn_set_params(pnn_net* n, int32_t which, const float* host_in) {
     if (!host_in) return fail(n, PNN_EINVAL, "host_in is NULL");
     if (which < -2 || which >= n->cfg.replicas) return fail(n, PNN_EINVAL, "which = %d out of range", which);
     HIP_TRY(n, hipDeviceSynchronize());
-    TRY(check_abort(n, true));
+    TRY(check_abort(n, true, nullptr));
     TRY(settle(n, nullptr));
     std::vector<float> padded(n->pstride);
     unpack(n, host_in, padded.data());
