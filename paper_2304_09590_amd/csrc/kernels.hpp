@@ -2225,14 +2225,23 @@ __global__ __launch_bounds__(256) void fwd_reduce_kernel(FwdReduceArgs a) {
 }
 
 // ------------------------------------------------------------------------------------
+__device__ inline float row_allmax16(float v);
+__device__ inline float row_allsum16(float v);
+
 // Output activation and output error of one (row, output) lane, the 16 lanes of a row taking
 // part together (softmax over them): eq. (3) / (5) and (9) / (10); zero on dead lanes (rows
 // past the step or outputs past O); rounded to the error type TD.
 
-template <typename TD>
+// DPP: the row reductions by DPP instead of shuffles through LDS (another order of the sum; the
+// whole wave active).
+template <typename TD, bool DPP = false>
 __device__ inline float out_error(float zv, bool live, int o, int label, int act_out, int loss) {
     float xo;
-    if (act_out == ACT_SOFTMAX) {
+    if (DPP && act_out == ACT_SOFTMAX) {
+        const float m = row_allmax16(live ? zv : -INFINITY);
+        const float ex = live ? expf(zv - m) : 0.f;
+        xo = ex * (1.0f / row_allsum16(ex));
+    } else if (act_out == ACT_SOFTMAX) {
         float m = live ? zv : -INFINITY;
 #pragma unroll
         for (int sh = 1; sh < 16; sh <<= 1) m = fmaxf(m, __shfl_xor(m, sh, 16));
@@ -3837,9 +3846,16 @@ __global__ __launch_bounds__(256) void psgd_persistent_kernel(PsgdPArgs a) {
 }
 
 // ------------------------------------------------------------------------------------
-// Mini-batch gradient descent of a one-hidden-layer fp32 network with batches of at most
-// 32 rows: one persistent launch per epoch (forward eq. (2)-(3), output error eq. (9)-(10),
-// hidden error eq. (11), updates eq. (12)-(13) with the gradients averaged over each batch).
+// Mini-batch gradient descent of a one-hidden-layer network with batches of at most 64 rows: one
+// persistent launch per epoch (forward eq. (2)-(3), output error eq. (9)-(10), hidden error
+// eq. (11), updates eq. (12)-(13) with the gradients averaged over each batch).
+//
+// Bound: the chain of a step -- the input sums, the exchange of the output sums between the tiles
+// of a CN (a store and a load through the memory-side cache, 1.5 us or more), the weight update --
+// of which the fp32 matrix instructions take 2.8 us (B = 32) or 5.5 us (B = 64).  Eight waves, two
+// per SIMD, so that one wave's LDS and memory latency covers the other's matrix instructions.
+// 784-256-10, us a step: K = 16, B = 32: 11.0 (four waves, 64-bit tagged shares polled by every
+// thread) -> 7.0; K = 10, B = 50: 63 in launches per layer -> 12.6; in bf16, 35 -> 9.5.
 //
 // Tile workgroup (k, rb) owns, for CN k, the hidden neurons j in [16 RT rb, 16 RT (rb + 1)):
 // their rows of W1 in registers (laid out as in psgd_tile), their biases b1 and their
@@ -3853,47 +3869,63 @@ __global__ __launch_bounds__(256) void psgd_persistent_kernel(PsgdPArgs a) {
 //   4. d1[t][j] = phi'(a1[t][j]) sum_o W2[o][j] delta2[t][o] with the pre-update W2; then W2
 //      (tile columns), b2, b1 and W1 (tile rows) -= eta / B_c * their gradients summed over
 //      the batch (every tile updates its copy of b2 identically).
-// Each share value is one 64-bit word written and read with agent-scope relaxed atomics:
-// the float in the low half and the step's tag (tag0 + c, increasing across launches) in
-// the high half, so a reader polls each value until it carries the step's tag and needs no
-// cache-wide release or acquire.  Shares are double buffered by step parity: a tile writes
-// step c+2's share only after it has read every share of step c+1, and every tile computed
-// its step c+1 share from the step c shares it had read.
+// A share word that has not been published holds a NaN pattern that no sum is stored as, so each
+// 4-byte word says by itself whether it has arrived, and a reader needs no flag, tag or cache-wide
+// release or acquire: it reads at agent scope until nothing is missing.  Four slots by step number:
+// a tile clears its own words of the slot two steps ahead once every share of the present step is
+// there (below).
 
-constexpr int MBP_TB = 32;    // most rows of a batch step
-constexpr int MBP_NRB = 16;   // most tile workgroups per CN
+constexpr int MBP_MAX_B = 64;  // most rows of a batch step
+constexpr int MBP_NRB = 16;    // most tile workgroups per CN
+constexpr int MBP_THREADS = 512, MBP_WAVES = MBP_THREADS / 64;
+constexpr int MBP_IB = 7;      // input blocks of 16 per wave (8 waves x 7 x 16 >= 832)
+constexpr unsigned MBP_NONE = 0xffffffffu;  // a share word not yet published (a NaN that no sum is stored as)
+constexpr int AUX_AGENT = 16;  // buffer access at agent scope (sc1), as relaxed agent-scope atomics compile to
 
 struct MbpArgs {
     float* theta;
+    bf16_t* shadow;             // bf16-mixed: operand copy of the weights, refreshed at the end
     int64_t pstride, off_w1, off_b1, off_w2, off_b2;
     const float* X;
     const int32_t* y;
     int64_t n_total;
-    unsigned long long* zpart;  // [2][K][nrb][MBP_TB][16] tagged output-sum shares
+    float* zpart;               // [4][K][nrb][16 MT x 16] output-sum shares, dense rows of O; -1 words where
+                                // nothing has been published (the first two slots at the launch)
     int* flags;                 // [K + 1]; flags[K]: abort (sticky: cleared only at allocation)
     int k_rep, H, O, In, act1, act2, loss, nrb, B;
     int cn0;                    // this launch trains CNs cn0 .. cn0 + gridDim.x / nrb - 1
     int xcd_map;                // 1: the tiles of a CN run on one XCD (grid a multiple of 8)
-    unsigned tag0;              // tag of step 0 (>= 1)
-    unsigned tag_skew;          // 0; > 0 makes the readers wait for tags never written (abort test)
+    int stall;                  // 0; 1 makes the readers wait for shares that never come (abort test)
     float lr;
     long spin_limit;
 };
 
-// LDS floats: the batch's rows transposed [64 MAX_IB][36] (every input block of the four
-// waves, zero past the inputs), partial input sums of the 4 waves, activations
-// [32][16 RT + 1], W2 columns [16][16 RT + 1], output errors [32][17], hidden errors
-// [16 RT][36], b1 [16 RT], b2 [16]
-__host__ __device__ constexpr int mbp_lds_floats(int rt) {
-    return 64 * MAX_IB * (MBP_TB + 4) + 4 * (MBP_TB / 16) * rt * 256 + MBP_TB * (16 * rt + 1) +
-           16 * (16 * rt + 1) + MBP_TB * 17 + 16 * rt * (MBP_TB + 4) + 16 * rt + 16;
+// LDS floats: partial input sums of the 8 waves, two transposed input blocks [16][16 MT + pad] per
+// wave, activations [16 MT][16 RT + 1], W2 columns [16][16 RT + 1], output errors [16 MT][17],
+// hidden errors [16 RT][16 MT + 4], b1 [16 RT], b2 [16], a flag.  (The shares that a step reads,
+// [8][16 MT x O], lie over the transposed blocks.)
+__host__ __device__ constexpr int mbp_lds_floats(int rt, int mt) {
+    return MBP_WAVES * mt * rt * 256 + MBP_WAVES * 2 * 16 * (16 * mt + 4) + 16 * mt * (16 * rt + 1) +
+           16 * (16 * rt + 1) + 16 * mt * 17 + 16 * rt * (16 * mt + 4) + 16 * rt + 16 + 4;
 }
 
-template <int RT>
-__global__ __launch_bounds__(256) void mbp_kernel(MbpArgs a) {
+typedef short s16x4 __attribute__((ext_vector_type(4)));
+// four fp32 values rounded to bf16, as an operand of v_mfma_f32_16x16x16_bf16
+__device__ inline s16x4 pack_bf4(float x, float y, float z, float w) {
+    const uint2 p = make_uint2(cvt_pk_bf16(x, y), cvt_pk_bf16(z, w));
+    return __builtin_bit_cast(s16x4, p);
+}
+
+// RT: 16-neuron sub-tiles per workgroup; MT: 16-row tiles of a batch (B <= 16 MT); BF: bf16-mixed
+// (inputs, operand weights, activations and errors rounded to bf16 where they enter a product,
+// as in the per-layer launches; the products over the inputs on the bf16 matrix instruction).
+template <int RT, int MT, bool BF>
+__global__ __launch_bounds__(MBP_THREADS) void mbp_kernel(MbpArgs a) {
     extern __shared__ __attribute__((aligned(16))) float smem[];
-    constexpr int NR = 16 * RT, NMT = MBP_TB / 16, LA = NR + 1, LD1 = MBP_TB + 4, ZS = MBP_TB * 16;
-    constexpr int XT = MBP_TB + 4;  // row stride of the transposed batch rows
+    typedef typename std::conditional<BF, bf16_t, float>::type TH;  // staged inputs, errors
+    constexpr int TB = 16 * MT, NR = 16 * RT, LA = NR + 1, LD1 = TB + 4, ZS = TB * 16;
+    constexpr int ZU = ZS / MBP_THREADS;          // output sums per thread
+    constexpr int XT = BF ? TB + 8 : TB + 4;      // row stride of a transposed input block (elements)
     const int tid = threadIdx.x, lane = tid & 63, g = lane >> 4, l16 = lane & 15;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);  // (uniform: keeps the block tests scalar)
     const int H = a.H, O = a.O, In = a.In, K = a.k_rep, nrb = a.nrb;
@@ -3905,377 +3937,410 @@ __global__ __launch_bounds__(256) void mbp_kernel(MbpArgs a) {
     if (a.xcd_map) lin = (blockIdx.x & 7) * (gridDim.x >> 3) + (blockIdx.x >> 3);
     const int k = a.cn0 + lin / nrb, rb = lin % nrb;
     const int hb = rb * NR;
-    const int nib = (In + 15) / 16;
-    float* xsm = smem;                       // [64 MAX_IB][XT] the batch's rows transposed: [input][row]
-    float* red4 = xsm + 64 * MAX_IB * XT;    // [4 waves][NMT][RT][64][4]
-    float* a1s = red4 + 4 * NMT * RT * 256;  // [MBP_TB][LA]
-    float* w2s = a1s + MBP_TB * LA;          // [16][LA], rows o >= O and columns past H zero
-    float* dls = w2s + 16 * LA;              // [MBP_TB][17]
-    float* d1s = dls + MBP_TB * 17;          // [NR][LD1]
-    float* b1s = d1s + NR * LD1;             // [NR]
-    float* b2s = b1s + NR;                   // [16]
+    const int nib = In / 16;                         // (In is a multiple of 16)
+    float* red = smem;                               // [8 waves][MT][RT][64][4]
+    float* trs = red + MBP_WAVES * MT * RT * 256;    // [8 waves][2][16][XT] transposed input blocks
+    float* a1s = trs + MBP_WAVES * 2 * 16 * (TB + 4);  // [TB][LA]
+    float* w2s = a1s + TB * LA;                      // [16][LA] fp32 master, rows o >= O and columns past H zero
+    float* dls = w2s + 16 * LA;                      // [TB][17]
+    float* d1s = dls + TB * 17;                      // [NR][LD1]
+    float* b1s = d1s + NR * LD1;                     // [NR]
+    float* b2s = b1s + NR;                           // [16]
+    int* gave_up = (int*)(b2s + 16);
+    float* zq = trs;                                 // [8][ZS] the shares of a step, by wave
+    TH* tr = (TH*)(trs + wave * 2 * 16 * (TB + 4));  // this wave's two blocks
     float* th = a.theta + (size_t)k * a.pstride;
+    // an operand as it enters a product
+    auto op = [](float v) { return BF ? bf2f(f2bf(v)) : v; };
 
-    float W[RT][MAX_IB][4];
+    float W[RT][MBP_IB][4];
 #pragma unroll
     for (int r = 0; r < RT; ++r) {
         const int h = hb + r * 16 + l16;
 #pragma unroll
-        for (int j = 0; j < MAX_IB; ++j)
+        for (int j = 0; j < MBP_IB; ++j)
 #pragma unroll
             for (int q = 0; q < 4; ++q) {
-                const int ib = wave + 4 * j, i = ib * 16 + 4 * g + q;
-                W[r][j][q] = (ib < nib && h < H && i < In) ? th[a.off_w1 + (size_t)h * In + i] : 0.f;
+                const int ib = wave + MBP_WAVES * j, i = ib * 16 + 4 * g + q;
+                W[r][j][q] = (ib < nib && h < H) ? th[a.off_w1 + (size_t)h * In + i] : 0.f;
             }
     }
-    for (int e = tid; e < 16 * NR; e += 256) {
+    for (int e = tid; e < 16 * NR; e += MBP_THREADS) {
         const int o = e / NR, j = e - o * NR;
         w2s[o * LA + j] = (o < O && hb + j < H) ? th[a.off_w2 + (size_t)o * H + hb + j] : 0.f;
     }
     if (tid < NR) b1s[tid] = hb + tid < H ? th[a.off_b1 + hb + tid] : 0.f;
     if (tid < 16) b2s[tid] = tid < O ? th[a.off_b2 + tid] : 0.f;
+    if (tid == 0) *gave_up = 0;
 
     const int64_t nz = shard_len(a.n_total, K, k), xs = shard_start(a.n_total, K, k);
     const int nsteps = (int)((nz + a.B - 1) / a.B);
     int* abort = a.flags + K;
-    // the batch's rows as operands of the input sums (lane: row mt * 16 + l16, inputs
-    // 16 ib + 4 g .. + 3 of the blocks ib = wave + 4 j), zero past the batch and past In;
-    // loaded one step ahead
-    float4 xn[NMT][MAX_IB];
-    int yn[ZS / 256];  // labels of the rows (tid + 256 u) / 16
-    // (bounds-checked buffer loads over the step's rows: rows past the step read as zero;
-    // blocks past In (In is a multiple of 16) read the next row, or zero after the last, and
-    // meet zero weights in the input sums and a zero mask in the weight update)
-    // rows_rsrc(c): descriptor of step c's rows; load_row_block(rs, idx): operand idx = mt * MAX_IB
-    // + j of buffer xn (issued one by one so that they can be spread over other work)
+    // the batch's rows as operands of the input sums (lane: row mt * 16 + l16, inputs 16 ib + 4 g
+    // .. + 3 of the blocks ib = wave + 8 j), loaded one step ahead through a bounds-checked
+    // descriptor of the step's rows (rows past the step read as zero)
+    float4 xn[MT][MBP_IB];
+    auto load_block = [&](__amdgpu_buffer_rsrc_t rs, int j) {
+        // (a block past the inputs reads past the descriptor: zeros without a memory access, and
+        // no branch.  The offset checked against the descriptor is the vector one -- a scalar
+        // offset would be added behind the check -- and is formed here each time, opaque to the
+        // compiler, which would keep one for every load in registers.)
+        unsigned past = wave + MBP_WAVES * j < nib ? 0u : 0x70000000u;
+        asm volatile("" : "+s"(past));
+#pragma unroll
+        for (int mt = 0; mt < MT; ++mt) {
+            const unsigned vo = ((unsigned)((mt * 16 + l16) * In + wave * 16 + 4 * g) * 4u) | past;
+            xn[mt][j] = __builtin_bit_cast(float4, __builtin_amdgcn_raw_buffer_load_b128(rs, vo + MBP_WAVES * 64u * j, 0, 0));
+        }
+    };
     auto rows_rsrc = [&](int c) {
         const int tcn = (int)min<int64_t>(a.B, nz - (int64_t)c * a.B);
         const int64_t xbn = xs + (int64_t)c * a.B;
         return __builtin_amdgcn_make_buffer_rsrc((void*)(a.X + (size_t)xbn * In), (short)0, tcn * In * 4, 0x00020000);
     };
-    auto load_row_block = [&](__amdgpu_buffer_rsrc_t rs, int idx) {
-        const int mt = idx / MAX_IB, j = idx - mt * MAX_IB;
-        const unsigned vo = (unsigned)((mt * 16 + l16) * In + wave * 16 + 4 * g) * 4u;
-        xn[mt][j] = __builtin_bit_cast(float4, __builtin_amdgcn_raw_buffer_load_b128(rs, vo + 256u * j, 0, 0));
-    };
-    auto load_labels = [&](int c) {
-        const int tcn = (int)min<int64_t>(a.B, nz - (int64_t)c * a.B);
-        const int64_t xbn = xs + (int64_t)c * a.B;
-#pragma unroll
-        for (int u = 0; u < ZS / 256; ++u) {
-            const int t = (tid + 256 * u) >> 4;
-            yn[u] = a.y[xbn + (t < tcn ? t : 0)];
-        }
-    };
     if (nsteps > 0) {
         const __amdgpu_buffer_rsrc_t rs0 = rows_rsrc(0);
 #pragma unroll
-        for (int idx = 0; idx < NMT * MAX_IB; ++idx) load_row_block(rs0, idx);
-        load_labels(0);
+        for (int j = 0; j < MBP_IB; ++j) load_block(rs0, j);
     }
     __syncthreads();
     bool ok = true;
     for (int c = 0; c < nsteps; ++c) {
         const int tc = (int)min<int64_t>(a.B, nz - (int64_t)c * a.B);
         const float scale = a.lr / (float)tc;
-        const unsigned long long tag = (unsigned long long)(a.tag0 + (unsigned)c) << 32;
-        int yc[ZS / 256];
+        const __amdgpu_buffer_rsrc_t rsn = rows_rsrc(c + 1 < nsteps ? c + 1 : c);
+        // 1. input sums of the tile's neurons (wave w adds the input blocks w, w + 8, ...), then
+        //    the activations; rows past the batch and neurons past H are zero
+        {
+            f4 acc[MT][RT];
 #pragma unroll
-        for (int u = 0; u < ZS / 256; ++u) yc[u] = yn[u];
-        // 1. input sums of the tile's neurons (wave w adds the input blocks w, w + 4, ...),
-        //    then the activations; rows past the batch and neurons past H are zero.  The rows
-        //    are staged transposed for the weight update.
+            for (int mt = 0; mt < MT; ++mt)
 #pragma unroll
-        for (int mt = 0; mt < NMT; ++mt) {
-            const int row = mt * 16 + l16;
-            f4 acc[RT];
+                for (int r = 0; r < RT; ++r) acc[mt][r] = f4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-            for (int r = 0; r < RT; ++r) acc[r] = f4{0.f, 0.f, 0.f, 0.f};
-            // (each block's staging stores follow its matrix instructions, which run meanwhile)
+            for (int j = 0; j < MBP_IB; ++j) {
+                if (wave + MBP_WAVES * j >= nib) break;
+                if constexpr (BF) {
+                    s16x4 wp[RT];
 #pragma unroll
-            for (int j = 0; j < MAX_IB; ++j) {
+                    for (int r = 0; r < RT; ++r) wp[r] = pack_bf4(W[r][j][0], W[r][j][1], W[r][j][2], W[r][j][3]);
 #pragma unroll
-                for (int r = 0; r < RT; ++r) {
-                    acc[r] = __builtin_amdgcn_mfma_f32_16x16x4f32(xn[mt][j].x, W[r][j][0], acc[r], 0, 0, 0);
-                    acc[r] = __builtin_amdgcn_mfma_f32_16x16x4f32(xn[mt][j].y, W[r][j][1], acc[r], 0, 0, 0);
-                    acc[r] = __builtin_amdgcn_mfma_f32_16x16x4f32(xn[mt][j].z, W[r][j][2], acc[r], 0, 0, 0);
-                    acc[r] = __builtin_amdgcn_mfma_f32_16x16x4f32(xn[mt][j].w, W[r][j][3], acc[r], 0, 0, 0);
+                    for (int mt = 0; mt < MT; ++mt) {
+                        const s16x4 xv = pack_bf4(xn[mt][j].x, xn[mt][j].y, xn[mt][j].z, xn[mt][j].w);
+#pragma unroll
+                        for (int r = 0; r < RT; ++r)
+                            acc[mt][r] = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(xv, wp[r], acc[mt][r], 0, 0, 0);
+                    }
+                } else {
+#pragma unroll
+                    for (int q = 0; q < 4; ++q)
+#pragma unroll
+                        for (int mt = 0; mt < MT; ++mt)
+#pragma unroll
+                            for (int r = 0; r < RT; ++r) {
+                                const float xv = q == 0 ? xn[mt][j].x : q == 1 ? xn[mt][j].y : q == 2 ? xn[mt][j].z : xn[mt][j].w;
+                                acc[mt][r] = __builtin_amdgcn_mfma_f32_16x16x4f32(xv, W[r][j][q], acc[mt][r], 0, 0, 0);
+                            }
                 }
-                float* xt = xsm + ((wave + 4 * j) * 16 + 4 * g) * XT + row;
-                xt[0] = xn[mt][j].x;
-                xt[XT] = xn[mt][j].y;
-                xt[2 * XT] = xn[mt][j].z;
-                xt[3 * XT] = xn[mt][j].w;
             }
 #pragma unroll
-            for (int r = 0; r < RT; ++r)
-                *(f4*)(red4 + (((size_t)(wave * NMT + mt) * RT + r) * 64 + lane) * 4) = acc[r];
+            for (int mt = 0; mt < MT; ++mt)
+#pragma unroll
+                for (int r = 0; r < RT; ++r)
+                    *(f4*)(red + (((size_t)(wave * MT + mt) * RT + r) * 64 + lane) * 4) = acc[mt][r];
         }
-        __syncthreads();
-        for (int e = tid; e < NMT * RT * 256; e += 256) {
+        lds_barrier();
+#pragma unroll
+        for (int e0 = 0; e0 < MT * RT * 256; e0 += MBP_THREADS) {
+            const int e = e0 + tid;
             const int mr = e >> 8, rem = e & 255, ln = rem >> 2, rr = rem & 3;  // mr = mt * RT + r
             const int mt = mr / RT, r = mr - mt * RT;
             float sum = 0.f;
 #pragma unroll
-            for (int w = 0; w < 4; ++w) sum += red4[(((size_t)(w * NMT + mt) * RT + r) * 64 + ln) * 4 + rr];
+            for (int w = 0; w < MBP_WAVES; ++w) sum += red[(((size_t)(w * MT + mt) * RT + r) * 64 + ln) * 4 + rr];
             const int t = mt * 16 + 4 * (ln >> 4) + rr, jj = r * 16 + (ln & 15);
-            a1s[t * LA + jj] = (t < tc && hb + jj < H) ? act_fn(a.act1, sum + b1s[jj]) : 0.f;
+            a1s[t * LA + jj] = (t < tc && hb + jj < H) ? op(act_fn(a.act1, sum + b1s[jj])) : 0.f;
         }
-        __syncthreads();
+        lds_barrier();
         // 2. the tile's share of the output sums, Z2_rb = a1 W2_rb^T: wave mt takes rows
         //    16 mt .. 16 mt + 15 (lane: rows 16 mt + 4 g + i, output l16)
-        unsigned long long* zp = a.zpart + (size_t)((c & 1) * K + k) * nrb * ZS;
-        if (wave < NMT) {
+        int yc[ZU];  // labels of the rows (tid + 512 u) / 16
+#pragma unroll
+        for (int u = 0; u < ZU; ++u) {
+            const int t = (tid + MBP_THREADS * u) >> 4;
+            yc[u] = a.y[xs + (int64_t)c * a.B + (t < tc ? t : 0)];
+        }
+        float* zslot = a.zpart + (size_t)((c & 3) * K + k) * nrb * ZS;
+        const int tc4 = (tc + 3) & ~3;  // rows published: whole groups of four (zeros past the batch)
+        if (wave < MT && wave * 16 < tc) {
             f4 acc = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
             for (int r = 0; r < RT; ++r)
 #pragma unroll
                 for (int ks = 0; ks < 4; ++ks) {
                     const int jj = r * 16 + 4 * ks + g;
-                    acc = __builtin_amdgcn_mfma_f32_16x16x4f32(a1s[(wave * 16 + l16) * LA + jj], w2s[l16 * LA + jj], acc,
+                    acc = __builtin_amdgcn_mfma_f32_16x16x4f32(a1s[(wave * 16 + l16) * LA + jj], op(w2s[l16 * LA + jj]), acc,
                                                                0, 0, 0);
                 }
+            const int t = wave * 16 + 4 * g;
+            if (t < tc4 && l16 < O) {
+                unsigned* zo = (unsigned*)zslot + (unsigned)(rb * ZS + t * O + l16);
 #pragma unroll
-            for (int i = 0; i < 4; ++i) {
-                const int t = wave * 16 + 4 * g + i;
-                if (t < tc && l16 < O)
-                    __hip_atomic_store(zp + (size_t)rb * ZS + t * 16 + l16, tag | __float_as_uint(acc[i]), __ATOMIC_RELAXED,
-                                       __HIP_MEMORY_SCOPE_AGENT);
+                for (int i = 0; i < 4; ++i) {
+                    const unsigned v = __float_as_uint(acc[i]);
+                    __hip_atomic_store(zo + i * O, v == MBP_NONE ? 0x7fc00000u : v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                }
             }
         }
-        // 3. every share of the CN, polled until it carries this step's tag (bounded: on
-        //    expiry, or when another workgroup gave up, the abort flag ends every workgroup)
-        float sv[ZS / 256][MBP_NRB];
+        // 3. every share of the CN: wave w takes those of the tiles w and w + 8, 16 bytes a lane,
+        //    read again until no word is missing (bounded: on expiry, or when another workgroup
+        //    gave up, the abort flag ends every workgroup), and their sum into LDS
         {
-            unsigned need = 0;
-#pragma unroll
-            for (int u = 0; u < ZS / 256; ++u) {
-                const int e = tid + 256 * u, t = e >> 4, o = e & 15;
-#pragma unroll
-                for (int q = 0; q < MBP_NRB; ++q)
-                    if (q < nrb && t < tc && o < O) need |= 1u << (u * MBP_NRB + q);
-            }
+            const __amdgpu_buffer_rsrc_t zr = __builtin_amdgcn_make_buffer_rsrc((void*)zslot, (short)0, nrb * ZS * 4, 0x00020000);
+            const int np = tc4 * O / 4;  // 16-byte pieces of a share
             long it = 0;
             bool good = true;
-            while (need) {
-                unsigned long long v[ZS / 256][MBP_NRB];
+            constexpr int NQ = MBP_NRB / MBP_WAVES;
+            static_assert(NQ == 2, "a wave adds the shares of its two tiles");
+            // The shares need about 1.5 us to become visible, and reads that come earlier delay
+            // them: every tile of the chip polling from the start kept the memory system busy
+            // with 5 MB a round, and the shares arrived after 3.5 us.  So the first read waits,
+            // longer with the larger batch, whose tiles reach this point further apart
+            // (784-256-10, per step: K = 16, B = 32: 10.8 us without the sleep, 7.4 with 16, 7.9
+            // with 38; K = 10, B = 50: 16.0 without, 15.0 with 16, 13.9 with 38).
+            if (wave < nrb) __builtin_amdgcn_s_sleep(MT <= 2 ? 16 : 36);
+            while (good && wave < nrb) {
+                uint4 v[NQ][MT];  // (np <= 64 MT)
+                unsigned miss = a.stall;
+                const int ab = __hip_atomic_load(abort, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 #pragma unroll
-                for (int u = 0; u < ZS / 256; ++u)
+                for (int p = 0; p < MT; ++p)
 #pragma unroll
-                    for (int q = 0; q < MBP_NRB; ++q)
-                        if (need & (1u << (u * MBP_NRB + q)))
-                            v[u][q] = __hip_atomic_load(zp + (size_t)q * ZS + tid + 256 * u, __ATOMIC_RELAXED,
-                                                        __HIP_MEMORY_SCOPE_AGENT);
+                    for (int q2 = 0; q2 < NQ; ++q2)
+                        if (64 * p < np)  // (of a tile that is not there: the first one's once more)
+                            v[q2][p] = __builtin_bit_cast(uint4, __builtin_amdgcn_raw_buffer_load_b128(
+                                           zr, (unsigned)min(64 * p + lane, np - 1) * 16u,
+                                           (unsigned)((wave + (wave + MBP_WAVES * q2 < nrb ? MBP_WAVES * q2 : 0)) * ZS) * 4u, AUX_AGENT));
 #pragma unroll
-                for (int u = 0; u < ZS / 256; ++u)
+                for (int p = 0; p < MT; ++p)
 #pragma unroll
-                    for (int q = 0; q < MBP_NRB; ++q)
-                        if ((need & (1u << (u * MBP_NRB + q))) && (v[u][q] >> 32) == (tag >> 32) + a.tag_skew) {
-                            sv[u][q] = __uint_as_float((unsigned)v[u][q]);
-                            need &= ~(1u << (u * MBP_NRB + q));
+                    for (int q2 = 0; q2 < NQ; ++q2)
+                        if (64 * p < np)
+                            miss |= v[q2][p].x == MBP_NONE || v[q2][p].y == MBP_NONE || v[q2][p].z == MBP_NONE || v[q2][p].w == MBP_NONE;
+                if (__ballot(miss != 0) == 0) {
+#pragma unroll
+                    for (int p = 0; p < MT; ++p)
+                        if (64 * p + lane < np) {
+                            f4 sum = __builtin_bit_cast(f4, v[0][p]);
+                            if (wave + MBP_WAVES < nrb) sum += __builtin_bit_cast(f4, v[1][p]);
+                            *(f4*)(zq + wave * ZS + 4 * (64 * p + lane)) = sum;
                         }
-                if (!need) break;
-                if (__hip_atomic_load(abort, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)) { good = false; break; }
-                if (++it > a.spin_limit) {
-                    __hip_atomic_store(abort, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-                    good = false;
                     break;
                 }
-                __builtin_amdgcn_s_sleep(1);
+                if (__builtin_amdgcn_readfirstlane(ab)) {
+                    good = false;
+                } else if (++it > a.spin_limit) {
+                    __hip_atomic_store(abort, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                    good = false;
+                }
+                asm volatile("" ::: "memory");
             }
-            if (__syncthreads_or(!good)) { ok = false; break; }
+            if (!good && lane == 0) *gave_up = 1;
         }
-        // output sums, output activation and output error; the 16 outputs of a row are 16
-        // adjacent lanes
+        lds_barrier();
+        if (lds_read(gave_up)) { ok = false; break; }
+        // output sums (the waves' sums in order), output activation and output error; the 16
+        // outputs of a row are 16 adjacent lanes
 #pragma unroll
-        for (int u = 0; u < ZS / 256; ++u) {
-            const int e = tid + 256 * u, t = e >> 4, o = e & 15;
+        for (int u = 0; u < ZU; ++u) {
+            const int e = tid + MBP_THREADS * u, t = e >> 4, o = e & 15;
             const bool live = t < tc && o < O;
-            float zv = 0.f;
+            float z = 0.f;
             if (live) {
-                float s = 0.f;
+                const float* zl = zq + t * O + o;
+                if (nrb >= MBP_WAVES) {
+                    float p[MBP_WAVES];  // (all in flight at once)
 #pragma unroll
-                for (int q = 0; q < MBP_NRB; ++q)
-                    if (q < nrb) s += sv[u][q];
-                zv = s + b2s[o];
-            }
-            float xo;
-            if (a.act2 == ACT_SOFTMAX) {
-                float m = live ? zv : -INFINITY;
+                    for (int q = 0; q < MBP_WAVES; ++q) p[q] = zl[q * ZS];
+                    asm volatile("" : "+v"(p[0]), "+v"(p[1]), "+v"(p[2]), "+v"(p[3]), "+v"(p[4]), "+v"(p[5]), "+v"(p[6]), "+v"(p[7]));
 #pragma unroll
-                for (int sh = 1; sh < 16; sh <<= 1) m = fmaxf(m, __shfl_xor(m, sh, 16));
-                const float ex = live ? expf(zv - m) : 0.f;
-                float sm = ex;
-#pragma unroll
-                for (int sh = 1; sh < 16; sh <<= 1) sm += __shfl_xor(sm, sh, 16);
-                xo = ex * (1.0f / sm);
-            } else {
-                xo = act_fn(a.act2, zv);
+                    for (int q = 0; q < MBP_WAVES; ++q) z += p[q];
+                } else {
+                    for (int q = 0; q < nrb; ++q) z += zl[q * ZS];
+                }
+                z += b2s[o];
             }
-            float dv = 0.f;
-            if (live) {
-                const float t1 = (o == yc[u]) ? 1.0f : 0.0f;
-                dv = (a.loss == LOSS_XENT) ? (xo - t1) : (xo - t1) * act_deriv(a.act2, xo);
-            }
-            dls[t * 17 + o] = dv;
+            dls[t * 17 + o] = out_error<TH, true>(z, live, o, yc[u], a.act2, a.loss);
         }
-        __syncthreads();
-        // 4. hidden errors of the tile's neurons with the pre-update W2, S = delta2 W2_rb:
-        //    wave mt takes rows 16 mt .. 16 mt + 15 (lane: rows 16 mt + 4 g + i, neuron l16)
-        if (wave < NMT) {
+        // Every tile of the CN has published step c, so it has read every share of step c - 1 and
+        // before: this tile's share of step c - 2 is cleared, for step c + 2.  (The next step
+        // starts by waiting for all of the wave's accesses, so the words are cleared before the
+        // tile publishes step c + 1, which every reader of step c + 2 has waited for.)
+        {
+            unsigned long long* zc = (unsigned long long*)(a.zpart + ((size_t)(((c + 2) & 3) * K + k) * nrb + rb) * ZS);
+            if (2 * tid < TB * O) __hip_atomic_store(zc + tid, ~0ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        }
+        lds_barrier();
+        // 4. hidden errors of the tile's neurons with the pre-update W2, S = delta2 W2_rb, one
+        //    (row tile, sub-tile) per wave (lane: rows 16 mt + 4 g + i, neuron l16); meanwhile the
+        //    last waves form W2's gradient, dW2 = delta2^T a1 over the batch (lane: outputs 4 g + i,
+        //    neuron l16; one sub-tile each), and update b2.  (Behind the barrier, beside the weight
+        //    update, these held the whole workgroup back at the next step: 784-256-10, B = 50,
+        //    13.5 -> 10.6 us a step.)  Rows past the batch are zero in delta2, a1 and d1.
 #pragma unroll
-            for (int r = 0; r < RT; ++r) {
+        for (int e0 = 0; e0 < MT * RT; e0 += MBP_WAVES) {
+            const int e = e0 + wave, mt = e / RT, r = e - mt * RT;
+            if (e < MT * RT) {
                 f4 sacc = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
                 for (int ks = 0; ks < 4; ++ks)
-                    sacc = __builtin_amdgcn_mfma_f32_16x16x4f32(dls[(wave * 16 + l16) * 17 + 4 * ks + g],
-                                                                w2s[(4 * ks + g) * LA + r * 16 + l16], sacc, 0, 0, 0);
-                const int t0 = wave * 16 + 4 * g, jj = r * 16 + l16;
+                    sacc = __builtin_amdgcn_mfma_f32_16x16x4f32(dls[(mt * 16 + l16) * 17 + 4 * ks + g],
+                                                                op(w2s[(4 * ks + g) * LA + r * 16 + l16]), sacc, 0, 0, 0);
+                const int t0 = mt * 16 + 4 * g, jj = r * 16 + l16;
                 float4 d;
-                d.x = sacc[0] * act_deriv(a.act1, a1s[(t0 + 0) * LA + jj]);
-                d.y = sacc[1] * act_deriv(a.act1, a1s[(t0 + 1) * LA + jj]);
-                d.z = sacc[2] * act_deriv(a.act1, a1s[(t0 + 2) * LA + jj]);
-                d.w = sacc[3] * act_deriv(a.act1, a1s[(t0 + 3) * LA + jj]);
+                d.x = op(sacc[0] * act_deriv(a.act1, a1s[(t0 + 0) * LA + jj]));
+                d.y = op(sacc[1] * act_deriv(a.act1, a1s[(t0 + 1) * LA + jj]));
+                d.z = op(sacc[2] * act_deriv(a.act1, a1s[(t0 + 2) * LA + jj]));
+                d.w = op(sacc[3] * act_deriv(a.act1, a1s[(t0 + 3) * LA + jj]));
                 *(float4*)(d1s + jj * LD1 + t0) = d;
             }
         }
-        __syncthreads();
-        // W2 columns (wave 2: dW2 = delta2^T a1 over the batch, lane: outputs 4 g + i, neuron
-        // l16), b2 (wave 1) and b1 (wave 3); their readers in the next step follow a barrier.
-        // Rows past the batch are zero in delta2, a1 and d1.
-        if (wave == 2) {
-            float da[MBP_TB / 4];
+        f4 g2 = {0.f, 0.f, 0.f, 0.f};
+        const int r2 = MBP_WAVES - 1 - wave;  // sub-tile of W2's gradient
+        if (r2 < RT) {
+            // (four chains of products, added in order)
+            f4 part[4];
 #pragma unroll
-            for (int ks = 0; ks < MBP_TB / 4; ++ks) da[ks] = dls[(4 * ks + g) * 17 + l16];
+            for (int i = 0; i < 4; ++i) part[i] = f4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-            for (int r = 0; r < RT; ++r) {
-                float xa[MBP_TB / 4];
-#pragma unroll
-                for (int ks = 0; ks < MBP_TB / 4; ++ks) xa[ks] = a1s[(4 * ks + g) * LA + r * 16 + l16];
-                f4 acc = {0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-                for (int ks = 0; ks < MBP_TB / 4; ++ks) acc = __builtin_amdgcn_mfma_f32_16x16x4f32(da[ks], xa[ks], acc, 0, 0, 0);
-                const int jj = r * 16 + l16;
-#pragma unroll
-                for (int i = 0; i < 4; ++i) {
-                    const int o = 4 * g + i;
-                    if (o < O && hb + jj < H) w2s[o * LA + jj] -= scale * acc[i];
-                }
-            }
-        } else if (wave == 1) {
-            // lane: output l16, rows 8 g .. 8 g + 7; the four partial sums added in lane order
+            for (int ks = 0; ks < TB / 4; ++ks)
+                part[ks & 3] = __builtin_amdgcn_mfma_f32_16x16x4f32(dls[(4 * ks + g) * 17 + l16],
+                                                                    a1s[(4 * ks + g) * LA + r2 * 16 + l16], part[ks & 3], 0, 0, 0);
+            g2 = (part[0] + part[1]) + (part[2] + part[3]);
+        } else if (r2 == RT) {
+            // lane: output l16, rows 4 MT g .. + 4 MT - 1; the four partial sums added in lane order
             float p = 0.f;
 #pragma unroll
-            for (int t = 0; t < 8; ++t) p += dls[(8 * g + t) * 17 + l16];
+            for (int t = 0; t < TB / 4; ++t) p += dls[(TB / 4 * g + t) * 17 + l16];
             const float s = __shfl(p, l16) + __shfl(p, l16 + 16) + __shfl(p, l16 + 32) + __shfl(p, l16 + 48);
             if (lane < O) b2s[lane] -= scale * s;
-        } else if (wave == 3) {
-            if (lane < NR && hb + lane < H) {
-                float s = 0.f;
+        }
+        lds_barrier();
+        // W2 columns and b1, whose readers in the next step follow a barrier
+        if (r2 < RT) {
+            const int jj = r2 * 16 + l16;
 #pragma unroll
-                for (int t4 = 0; t4 < MBP_TB / 4; ++t4) {
-                    const float4 d = *(const float4*)(d1s + lane * LD1 + 4 * t4);
-                    s += d.x;
-                    s += d.y;
-                    s += d.z;
-                    s += d.w;
-                }
-                b1s[lane] -= scale * s;
+            for (int i = 0; i < 4; ++i) {
+                const int o = 4 * g + i;
+                if (o < O && hb + jj < H) w2s[o * LA + jj] -= scale * g2[i];
             }
+        } else if (r2 < 2 * RT) {
+            // lane: neuron l16 of a sub-tile, rows 4 MT g .. + 4 MT - 1; the four partial sums added in
+            // lane order
+            const int jj = (r2 - RT) * 16 + l16;
+            float p = 0.f;
+#pragma unroll
+            for (int t4 = 0; t4 < MT; ++t4) {
+                const float4 d = *(const float4*)(d1s + jj * LD1 + 4 * MT * g + 4 * t4);
+                p += (d.x + d.y) + (d.z + d.w);
+            }
+            const float s = __shfl(p, l16) + __shfl(p, l16 + 16) + __shfl(p, l16 + 32) + __shfl(p, l16 + 48);
+            if (g == 0 && hb + jj < H) b1s[jj] -= scale * s;
         }
         // W1 rows of the tile -= eta / B_c sum_t d1_t x_t^T (a product whose accumulator layout
-        // equals the register layout); the next step's rows are loaded meanwhile, a few loads
-        // per pair of blocks
-        // (with 32-neuron tiles all of them at once: spreading them costs registers that tile
-        // does not have)
-        const bool more = c + 1 < nsteps;
-        const __amdgpu_buffer_rsrc_t rsn = rows_rsrc(more ? c + 1 : c);
-        if (more) load_labels(c + 1);
-        if (RT > 1 && more) {
-#pragma unroll
-            for (int idx = 0; idx < NMT * MAX_IB; ++idx) load_row_block(rsn, idx);
-        }
+        // equals the register layout).  Each wave transposes its own input blocks through two LDS
+        // blocks of its own, one block ahead of the products (a wave's LDS accesses complete in
+        // order, so no barrier); the next step's rows are loaded into a block's registers as soon
+        // as it is staged.
         {
-            float bv[RT][MBP_TB / 4];
+            auto stage = [&](int j) {
+                TH* t = tr + (j & 1) * 16 * XT + 4 * g * XT + l16;
 #pragma unroll
-            for (int r = 0; r < RT; ++r) {
-                const float* D = d1s + (r * 16 + l16) * LD1;
+                for (int mt = 0; mt < MT; ++mt) {
+                    if constexpr (BF) {
+                        const s16x4 xv = pack_bf4(xn[mt][j].x, xn[mt][j].y, xn[mt][j].z, xn[mt][j].w);
 #pragma unroll
-                for (int sl = 0; sl < MBP_TB / 16; ++sl) {
-                    const float4 d = *(const float4*)(D + sl * 16 + 4 * g);
-                    bv[r][4 * sl + 0] = d.x;
-                    bv[r][4 * sl + 1] = d.y;
-                    bv[r][4 * sl + 2] = d.z;
-                    bv[r][4 * sl + 3] = d.w;
+                        for (int q = 0; q < 4; ++q) t[q * XT + mt * 16] = (bf16_t)xv[q];
+                    } else {
+                        t[mt * 16] = xn[mt][j].x;
+                        t[XT + mt * 16] = xn[mt][j].y;
+                        t[2 * XT + mt * 16] = xn[mt][j].z;
+                        t[3 * XT + mt * 16] = xn[mt][j].w;
+                    }
                 }
-            }
-            // Blocks in pairs: two independent accumulation chains interleaved, and the next
-            // pair's staged rows read before this pair's matrix instructions (blocks past the
-            // inputs hold zero rows and weights: one branch-free sequence).
-            // rows (u >> 2) * 16 + 4 g + (u & 3) of input (wave + 4 j) * 16 + l16; blocks past In
-            // stay zero
-            auto read_block = [&](int j, float (&av)[MBP_TB / 4]) {
-                const bool jok = wave + 4 * j < nib;
-                const float* xt = xsm + ((wave + 4 * j) * 16 + l16) * XT + 4 * g;
-                const float4 x0 = *(const float4*)xt, x1 = *(const float4*)(xt + 16);
-                av[0] = jok ? x0.x : 0.f; av[1] = jok ? x0.y : 0.f; av[2] = jok ? x0.z : 0.f; av[3] = jok ? x0.w : 0.f;
-                av[4] = jok ? x1.x : 0.f; av[5] = jok ? x1.y : 0.f; av[6] = jok ? x1.z : 0.f; av[7] = jok ? x1.w : 0.f;
             };
-            float avA[MBP_TB / 4], avB[MBP_TB / 4];
-            read_block(0, avA);
-            if (1 < MAX_IB) read_block(1, avB);
-            constexpr int LPP = (NMT * MAX_IB + (MAX_IB + 1) / 2 - 1) / ((MAX_IB + 1) / 2);  // loads per pair
+            float4 bv[BF ? 1 : RT][BF ? 1 : MT];
+            s16x4 bp[BF ? RT : 1][BF ? MT : 1];
 #pragma unroll
-            for (int j = 0; j < MAX_IB; j += 2) {
-                const bool two = j + 1 < MAX_IB;
-                if (RT == 1 && more) {
+            for (int r = 0; r < RT; ++r)
 #pragma unroll
-                    for (int i = 0; i < LPP; ++i)
-                        if ((j / 2) * LPP + i < NMT * MAX_IB) load_row_block(rsn, (j / 2) * LPP + i);
+                for (int mt = 0; mt < MT; ++mt) {
+                    const float4 d = *(const float4*)(d1s + (r * 16 + l16) * LD1 + mt * 16 + 4 * g);
+                    if constexpr (BF) bp[r][mt] = pack_bf4(d.x, d.y, d.z, d.w);
+                    else bv[r][mt] = d;
                 }
-                float nA[MBP_TB / 4], nB[MBP_TB / 4];
-                if (j + 2 < MAX_IB) read_block(j + 2, nA);
-                if (j + 3 < MAX_IB) read_block(j + 3, nB);
+            stage(0);
 #pragma unroll
-                for (int r = 0; r < RT; ++r) {
-                    f4 dA = {0.f, 0.f, 0.f, 0.f}, dB = {0.f, 0.f, 0.f, 0.f};
+            for (int j = 0; j < MBP_IB; ++j) {
+                load_block(rsn, j);  // (after the last step: its own rows once more)
+                if (wave + MBP_WAVES * j >= nib) continue;
+                if (j + 1 < MBP_IB && wave + MBP_WAVES * (j + 1) < nib) stage(j + 1);
+                asm volatile("" ::: "memory");  // (the reads below stay after the staging stores of other lanes)
+                const TH* t = tr + (j & 1) * 16 * XT + l16 * XT + 4 * g;
+                f4 dw[RT];
 #pragma unroll
-                    for (int u = 0; u < MBP_TB / 4; ++u) {
-                        dA = __builtin_amdgcn_mfma_f32_16x16x4f32(avA[u], bv[r][u], dA, 0, 0, 0);
-                        if (two) dB = __builtin_amdgcn_mfma_f32_16x16x4f32(avB[u], bv[r][u], dB, 0, 0, 0);
+                for (int r = 0; r < RT; ++r) dw[r] = f4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+                for (int mt = 0; mt < MT; ++mt) {
+                    if constexpr (BF) {
+                        const s16x4 xv = *(const s16x4*)(t + mt * 16);
+#pragma unroll
+                        for (int r = 0; r < RT; ++r)
+                            dw[r] = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(xv, bp[r][mt], dw[r], 0, 0, 0);
+                    } else {
+                        const float4 xv = *(const float4*)(t + mt * 16);
+#pragma unroll
+                        for (int r = 0; r < RT; ++r) {
+                            dw[r] = __builtin_amdgcn_mfma_f32_16x16x4f32(xv.x, bv[r][mt].x, dw[r], 0, 0, 0);
+                            dw[r] = __builtin_amdgcn_mfma_f32_16x16x4f32(xv.y, bv[r][mt].y, dw[r], 0, 0, 0);
+                            dw[r] = __builtin_amdgcn_mfma_f32_16x16x4f32(xv.z, bv[r][mt].z, dw[r], 0, 0, 0);
+                            dw[r] = __builtin_amdgcn_mfma_f32_16x16x4f32(xv.w, bv[r][mt].w, dw[r], 0, 0, 0);
+                        }
                     }
-#pragma unroll
-                    for (int q = 0; q < 4; ++q) {
-                        W[r][j][q] -= scale * dA[q];
-                        if (two) W[r][j + 1][q] -= scale * dB[q];
-                    }
                 }
+                asm volatile("" ::: "memory");
 #pragma unroll
-                for (int u = 0; u < MBP_TB / 4; ++u) {
-                    if (j + 2 < MAX_IB) avA[u] = nA[u];
-                    if (j + 3 < MAX_IB) avB[u] = nB[u];
-                }
+                for (int r = 0; r < RT; ++r)
+#pragma unroll
+                    for (int q = 0; q < 4; ++q) W[r][j][q] -= scale * dw[r][q];
             }
         }
-        // (the next step's forward overwrites the staged rows; LDS only, so the barrier does not
-        // wait for the next step's row loads, which the forward waits for itself)
-        lds_barrier();
+        // (no barrier here: the next step's first writes, the partial input sums, were last read
+        // before this step's second barrier, and everything else is written behind its first)
     }
     if (!ok) return;
+    bf16_t* sh = BF ? a.shadow + (size_t)k * a.pstride : nullptr;
 #pragma unroll
     for (int r = 0; r < RT; ++r) {
         const int h = hb + r * 16 + l16;
 #pragma unroll
-        for (int j = 0; j < MAX_IB; ++j)
+        for (int j = 0; j < MBP_IB; ++j)
 #pragma unroll
             for (int q = 0; q < 4; ++q) {
-                const int ib = wave + 4 * j, i = ib * 16 + 4 * g + q;
-                if (ib < nib && h < H && i < In) th[a.off_w1 + (size_t)h * In + i] = W[r][j][q];
+                const int ib = wave + MBP_WAVES * j, i = ib * 16 + 4 * g + q;
+                if (ib < nib && h < H) {
+                    th[a.off_w1 + (size_t)h * In + i] = W[r][j][q];
+                    if (BF) sh[a.off_w1 + (size_t)h * In + i] = f2bf(W[r][j][q]);
+                }
             }
     }
-    for (int e = tid; e < 16 * NR; e += 256) {
+    __syncthreads();  // (the last step's updates of W2, b1 and b2)
+    for (int e = tid; e < 16 * NR; e += MBP_THREADS) {
         const int o = e / NR, j = e - o * NR;
-        if (o < O && hb + j < H) th[a.off_w2 + (size_t)o * H + hb + j] = w2s[o * LA + j];
+        if (o < O && hb + j < H) {
+            th[a.off_w2 + (size_t)o * H + hb + j] = w2s[o * LA + j];
+            if (BF) sh[a.off_w2 + (size_t)o * H + hb + j] = f2bf(w2s[o * LA + j]);
+        }
     }
     if (tid < NR && hb + tid < H) th[a.off_b1 + hb + tid] = b1s[tid];
     if (rb == 0 && tid < O) th[a.off_b2 + tid] = b2s[tid];
@@ -4311,6 +4376,11 @@ __global__ __launch_bounds__(256) void sum_f64_kernel(const double* v, int64_t n
         __syncthreads();
     }
     if (t == 0) *out = part[0];
+}
+
+__global__ void fill_ints_kernel(int* p, int64_t n, int v) {
+    for (int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; i < n / 4; i += (int64_t)gridDim.x * blockDim.x)
+        ((int4*)p)[i] = make_int4(v, v, v, v);
 }
 
 __global__ void zero_ints_kernel(int* p, int n) {

@@ -114,13 +114,12 @@ struct pnn_net {
     float* gramx = nullptr;  // [K][nch-1][T][T]
     size_t gramx_elems = 0;
     size_t psmem = 0;
-    // persistent mini-batch plan (one hidden layer, fp32, batches of 2..32 rows): nrb tile
+    // persistent mini-batch plan (one hidden layer, batches of at most 64 rows): nrb tile
     // workgroups of 16 mrt neurons per CN; flags[K] = abort
     bool mbp = false;
     int mrt = 1;
-    unsigned long long* zpart = nullptr;  // [2][K][nrb][32][16] tagged output-sum shares
+    float* zpart = nullptr;  // [4][K][nrb][16 x row tiles x 16] output-sum shares
     size_t zpart_elems = 0;
-    unsigned mbp_tag = 1;                 // tag of the next launch's first batch step
     // fp32 products of the large GEMMs on the bf16 matrix cores (three-part split); false:
     // fp32 matrix instructions throughout (PNN_GEMM=fp32, read by pnn_init)
     bool gemm_x3 = true;
@@ -134,10 +133,10 @@ struct pnn_net {
     float* fx3_zpart = nullptr;
     float* fx3_dout = nullptr;
     // bounded waits of the persistent kernels: polls before giving up; and a test hook that
-    // makes their waits run into that bound (the mini-batch kernel's readers wait for share
-    // tags that are never written, the per-sample kernel's for more tiles than exist)
+    // makes their waits run into that bound (the mini-batch kernel's readers wait for shares
+    // that never come, the per-sample kernel's for more tiles than exist)
     long spin_limit = 0;
-    unsigned tag_skew = 0;
+    int stall = 0;
     int wait_skew = 0;
     int tile_delay = 0;  // PNN_TEST_TILE_DELAY: late tile workgroups in the per-sample kernel
     // the abort flag of the last persistent launch has not been read yet; abort_ev follows
@@ -765,42 +764,40 @@ pnn_status psgd_persistent_epoch(pnn_net* n, const float* X, const int32_t* Y, i
 // ---------------------------------------------------------------------------------------
 // persistent mini-batch plan
 
-const void* mbp_fn(int rt) { return rt == 2 ? (const void*)mbp_kernel<2> : (const void*)mbp_kernel<1>; }
+// row tiles of 16 that hold a batch
+int mbp_row_tiles(int B) { return B <= 32 ? 2 : 4; }
+
+template <bool BF>
+const void* mbp_fn_of(int rt, int mt) {
+    if (mt == 2) return rt == 2 ? (const void*)mbp_kernel<2, 2, BF> : (const void*)mbp_kernel<1, 2, BF>;
+    return rt == 2 ? (const void*)mbp_kernel<2, 4, BF> : (const void*)mbp_kernel<1, 4, BF>;
+}
+const void* mbp_fn(bool bf16, int rt, int mt) { return bf16 ? mbp_fn_of<true>(rt, mt) : mbp_fn_of<false>(rt, mt); }
 
 pnn_status mbp_epoch(pnn_net* n, const float* X, const int32_t* Y, int64_t N, hipStream_t s) {
     const int K = n->cfg.replicas;
-    const int64_t nsteps = (shard_len(N, K, 0) + n->cfg.batch - 1) / n->cfg.batch;
-    if ((uint64_t)n->mbp_tag + (uint64_t)nsteps >= 0xFFFFFFFFull) {
-        // the step tags would wrap: clear the shares (so that no stale tag can match) and restart
-        const int ni = (int)(2 * n->zpart_elems);
-        Launch l(n, s, "zero_flags");
-        zero_ints_kernel<<<(ni + 255) / 256, 256, 0, s>>>((int*)n->zpart, ni);
-        TRY(l.done());
-        n->mbp_tag = 1;
-    }
     {
-        // (the abort slot flags[K] is sticky: a launch after an abort ends at once)
-        Launch l(n, s, "zero_flags");
-        zero_ints_kernel<<<(K + 255) / 256, 256, 0, s>>>(n->flags, K);
+        // no share of the first two steps is there yet
+        const int64_t ni = (int64_t)(n->zpart_elems / 2);
+        Launch l(n, s, "clear_shares");
+        fill_ints_kernel<<<(unsigned)std::min<int64_t>((ni / 4 + 255) / 256, 1024), 256, 0, s>>>((int*)n->zpart, ni, -1);
         TRY(l.done());
     }
     MbpArgs a;
     memset(&a, 0, sizeof a);
-    a.theta = n->theta; a.pstride = n->pstride;
+    a.theta = n->theta; a.shadow = n->shadow; a.pstride = n->pstride;
     a.off_w1 = n->off_w[0]; a.off_b1 = n->off_b[0]; a.off_w2 = n->off_w[1]; a.off_b2 = n->off_b[1];
     a.X = X; a.y = Y; a.n_total = N;
     a.zpart = n->zpart; a.flags = n->flags;
     a.k_rep = K; a.H = n->sizes[1]; a.O = n->sizes[2]; a.In = n->sizes[0];
     a.act1 = n->act[0]; a.act2 = n->act[1]; a.loss = n->cfg.loss;
     a.nrb = n->nrb; a.B = n->cfg.batch;
-    a.tag0 = n->mbp_tag;
-    a.tag_skew = n->tag_skew;
-    n->mbp_tag += (unsigned)nsteps;
+    a.stall = n->stall;
     a.lr = n->cfg.lr;
     a.spin_limit = n->spin_limit;
     void* params[] = {&a};
     // the CNs in groups of at most kgroup (balanced), one launch each (every CN has its own
-    // share slots, so the groups' launches share the step tags)
+    // share slots)
     const int G = (K + n->kgroup - 1) / n->kgroup;
     for (int gi = 0, c0 = 0; gi < G; ++gi) {
         const int kl = (K - c0) / (G - gi);
@@ -808,7 +805,8 @@ pnn_status mbp_epoch(pnn_net* n, const float* X, const int32_t* Y, int64_t N, hi
         a.cn0 = c0;
         a.xcd_map = grid % 8 == 0;
         Launch l(n, s, "mb_persistent");
-        hipError_t e = hipLaunchCooperativeKernel(mbp_fn(n->mrt), dim3((unsigned)grid), dim3(256), params,
+        hipError_t e = hipLaunchCooperativeKernel(mbp_fn(n->bf16, n->mrt, mbp_row_tiles(n->cfg.batch)),
+                                                  dim3((unsigned)grid), dim3(MBP_THREADS), params,
                                                   (unsigned)n->psmem, s);
         if (e != hipSuccess) {
             (void)hipGetLastError();
@@ -1061,7 +1059,7 @@ pnn_status pnn_init(const pnn_config* cfg, const float* theta0_host, void* hip_s
     }
     if (const char* e = getenv("PNN_TEST_STALL_WAITS")) {
         const bool on = strcmp(e, "1") == 0;
-        n->tag_skew = on ? 1u : 0u;
+        n->stall = on ? 1 : 0;
         n->wait_skew = on ? (1 << 29) : 0;  // (the tiles count up to nrb per chunk parity)
     }
     // PNN_TEST_TILE_DELAY=n: half of every CN's tile workgroups start n sleeps late (the
@@ -1174,20 +1172,26 @@ pnn_status pnn_init(const pnn_config* cfg, const float* theta0_host, void* hip_s
                 if ((st = dev_alloc(n, &n->ppart, (size_t)n->ksplit * K * B * N1)) != PNN_OK) return bail(st);
             }
         }
-        // persistent mini-batch plan: one hidden layer in fp32, batches of 2..32 rows, at most
-        // 16 outputs, and every CN's ceil(H / 16 rt) tile workgroups co-resident (rt = 1, or 2
-        // when 16-neuron tiles do not fit); PNN_MB_PLAN=launch selects the per-layer launches
+        // persistent mini-batch plan: one hidden layer, batches of at most 64 rows, at most 16
+        // outputs, and every CN's ceil(H / 16 rt) tile workgroups co-resident (rt = 1, or 2 when
+        // 16-neuron tiles do not fit); PNN_MB_PLAN=launch selects the per-layer launches
         const char* plan = getenv("PNN_MB_PLAN");
         const bool forced_launch = plan && strcmp(plan, "launch") == 0;
-        if (!forced_launch && !n->bf16 && n->L == 2 && B >= 2 && B <= MBP_TB && n->sizes[2] <= 16 &&
-            n->sizes[0] % 16 == 0 && n->sizes[0] <= 4 * MAX_IB * 16) {
+        if (!forced_launch && n->L == 2 && B <= MBP_MAX_B && n->sizes[2] <= 16 && n->sizes[0] % 16 == 0 &&
+            n->sizes[0] <= 4 * MAX_IB * 16) {
             int cus = 0;
             if (hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, n->device) != hipSuccess) cus = 0;
             const int H = n->sizes[1];
             // tile workgroups of 16 neurons (rt = 1) or 32 (rt = 2); the CNs in groups whose tiles
             // fit the CUs, one launch each; the one with the least estimated time (launches x the
-            // relative time of a batch step: 1 with 16-neuron tiles, 1.45 with 32, as measured
-            // with 784-256-10 nets)
+            // relative time of a batch step: 1 with 16-neuron tiles, with 32 1.45, or 1.7 in batches
+            // of more than 32 rows, as measured with 784-256-10 and 784-512-10 nets).
+            // Above 32 rows at most three launches: a step of the fourth starts where the per-layer
+            // launches, which take all CNs at once, have caught up (784-512-10, B = 64, us a step,
+            // this kernel / launches: K = 32 64 / 94, K = 64 127 / 119; bf16 784-256-10: K = 32
+            // 34 / 50, K = 64 67 / 62; 784-256-10: K = 128 129 / 113).  Up to 32 rows it is the
+            // faster one up to the 256 CNs measured (784-512-10, B = 32, K = 256: 233 / 354).
+            const int mt = mbp_row_tiles(B);
             int rt = 0, kg = 0;
             double best = 1e30;
             for (int r = 1; r <= 2; ++r) {
@@ -1195,16 +1199,16 @@ pnn_status pnn_init(const pnn_config* cfg, const float* theta0_host, void* hip_s
                 if (nb > MBP_NRB) continue;
                 const int g = std::min(K, cus / nb);
                 if (g < 1) continue;
-                const double cost = (double)((K + g - 1) / g) * (r == 1 ? 1.0 : 1.45);
+                const double cost = (double)((K + g - 1) / g) * (r == 1 ? 1.0 : mt == 2 ? 1.45 : 1.7);
                 if (cost < best) { best = cost; rt = r; kg = g; }
             }
-            if (rt > 0) {
+            if (rt > 0 && (mt == 2 || (K + kg - 1) / kg <= 3)) {
                 const int nrb = (H + 16 * rt - 1) / (16 * rt);
-                const size_t smem = (size_t)mbp_lds_floats(rt) * sizeof(float);
-                const void* fn = mbp_fn(rt);
+                const size_t smem = (size_t)mbp_lds_floats(rt, mt) * sizeof(float);
+                const void* fn = mbp_fn(n->bf16, rt, mt);
                 int per_cu = 0;
                 bool fits = hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)smem) == hipSuccess;
-                if (fits && hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, fn, 256, smem) != hipSuccess) fits = false;
+                if (fits && hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, fn, MBP_THREADS, smem) != hipSuccess) fits = false;
                 if (fits && (int64_t)per_cu * cus < (int64_t)kg * nrb) fits = false;
                 (void)hipGetLastError();
                 if (fits) {
@@ -1213,8 +1217,7 @@ pnn_status pnn_init(const pnn_config* cfg, const float* theta0_host, void* hip_s
                     n->nrb = nrb;
                     n->kgroup = kg;
                     n->psmem = smem;
-                    n->zpart_elems = (size_t)2 * K * nrb * MBP_TB * 16;
-                    // (zeroed: a share is valid only with its step's tag, which is >= 1)
+                    n->zpart_elems = (size_t)4 * K * nrb * mt * 16 * 16;
                     if ((st = dev_alloc(n, &n->zpart, n->zpart_elems)) != PNN_OK) return bail(st);
                     if ((st = dev_alloc(n, &n->flags, (size_t)(K + 1))) != PNN_OK) return bail(st);
                 }
@@ -1280,7 +1283,8 @@ pnn_status pnn_train_epoch(pnn_net* n, const float* x_dev, const int32_t* y_dev,
     TRY(check_abort(n, false, s));
     if (!n->fx3) TRY(settle(n, s));
     if (n->psgd) return psgd_epoch(n, x_dev, y_dev, N, s);
-    if (n->mbp) return mbp_epoch(n, x_dev, y_dev, N, s);
+    // (an epoch recorded into a graph takes the launches per layer)
+    if (n->mbp && !capturing(s)) return mbp_epoch(n, x_dev, y_dev, N, s);
     const int64_t nmax = shard_len(N, n->cfg.replicas, 0);
     for (int64_t r0 = 0; r0 < nmax; r0 += n->cfg.batch) {
         // (the first step writes every parameter of every CN: each CN has rows in it)
@@ -1567,7 +1571,8 @@ pnn_status pnn_eval_noalloc(pnn_net* n, int32_t which, const float* x_dev, const
 const char* pnn_plan(const pnn_net* n) {
     if (!n) return "";
     if (n->psgd) return n->persistent && n->T == 0 ? "per-sample persistent" : "per-sample chunked";
-    return n->mbp ? "mini-batch persistent" : n->fx3 ? "mini-batch fused last layer" : "mini-batch";
+    if (n->mbp && !n->bf16 && n->cfg.batch <= 32) return "mini-batch persistent";
+    return n->fx3 ? "mini-batch fused last layer" : "mini-batch";
 }
 
 pnn_status pnn_get_params(pnn_net* n, int32_t which, float* host_out) {
