@@ -115,6 +115,10 @@ __device__ inline float act_fast(int a, float z) {
     }
 }
 
+// maximum / sum over the 16 lanes of a row, by DPP (defined with the other cross-lane helpers)
+__device__ inline float row_allmax16(float v);
+__device__ inline float row_allsum16(float v);
+
 __device__ inline float wave_sum(float v) {
 #pragma unroll
     for (int off = 32; off >= 1; off >>= 1) v += __shfl_xor(v, off, 64);
@@ -856,6 +860,124 @@ __global__ __launch_bounds__(256) void gemm_kw_kernel(GemmArgs g) {
             for (int r = 0; r < 4; ++r)
                 if (n + r < Nv) ((TO*)g.c)[ci + r] = from_f<TO>(act_fn(g.act, v[r] + bb[r]));
         }
+    }
+}
+
+// ------------------------------------------------------------------------------------
+// Forward product with few output tiles (fewer 64 x 64 tiles than CUs) and both operands along k:
+// (16 RT) x (16 RT) tiles, the eight waves of a workgroup split the contraction (fp32: wave w takes
+// the 16-deep blocks w, w + 8, ... on v_mfma_f32_16x16x4_f32; bf16: the 32-deep ones on
+// v_mfma_f32_16x16x32_bf16), fragments straight from global memory in the matrix instruction's
+// layout through buffer descriptors (rows past the tile and steps past K read zero), KS_PD steps
+// ahead.  The partial tiles meet in LDS and are added in pairs, with bias and activation.
+// Bound: latency -- the 64 x 64 tiles walk 49 k-tiles of a 784-long contraction one after another
+// on a handful of CUs, here a wave has 7 steps, all in flight at once or nearly.
+// Inference of 16 rows, 784 -> 128: 30 -> 7 us.  See ks_tile (pnn.hip) for the rule.
+constexpr int KS_WAVES = 8, KS_THREADS = 64 * KS_WAVES;
+
+template <bool BF, typename TA, typename TO, int RT>
+__global__ __launch_bounds__(KS_THREADS) void gemm_ks_kernel(GemmArgs g) {
+    constexpr int TS = 16 * RT, LD = TS + 1;
+    constexpr int BK = BF ? 32 : 16;              // contraction steps of a block
+    constexpr int EB = BF ? 2 : 4;                // bytes of a B element
+    constexpr int AV = BF ? sizeof(TA) / 2 : 1;   // 16-byte loads per A fragment
+    constexpr int PD = RT == 1 ? 4 : 2;           // blocks in flight
+    __shared__ float part[KS_WAVES][TS * LD];
+    const int tid = threadIdx.x, lane = tid & 63, rl = lane & 15, kg = lane >> 4;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    int bx, by, bz;
+    gemm_tile(bx, by, bz);
+    int cn, valid;
+    int64_t r0;
+    gemm_zinfo(g, bz, cn, r0, valid);
+    const int Mv = (g.sample_dims & 1) ? valid : g.M;
+    const int Nv = (g.sample_dims & 2) ? valid : g.N;
+    const int Kv = g.Kd;
+    const int m0 = by * TS, n0 = bx * TS;
+    if (m0 >= Mv || n0 >= Nv) return;
+    const int64_t xbase = shard_start(g.n_total, g.k_rep, cn) + r0;
+    const B3Src sa = b3_src<true, BF ? (int)sizeof(TA) : 4>(g.a, bz, cn, xbase, m0, Mv, Kv);
+    const B3Src sb = b3_src<true, EB>(g.b, bz, cn, xbase, n0, Nv, Kv);
+    f4 acc[RT][RT];
+#pragma unroll
+    for (int i = 0; i < RT; ++i)
+#pragma unroll
+        for (int j = 0; j < RT; ++j) acc[i][j] = f4{0.f, 0.f, 0.f, 0.f};
+    uint4 fa[PD][RT][AV], fb[PD][RT];
+    auto load = [&](int p, int blk) {
+        const int k = BK * blk + (BF ? 8 : 4) * kg;
+        const uint32_t inv = (uint32_t)(Kv - 1 - k) >> 31;
+#pragma unroll
+        for (int i = 0; i < RT; ++i) {
+            const uint32_t o = ((uint32_t)(16 * i + rl) * sa.ld4 + (uint32_t)k * (uint32_t)sizeof(TA)) | (inv << 31);
+#pragma unroll
+            for (int v = 0; v < AV; ++v)
+                fa[p][i][v] = __builtin_bit_cast(uint4, __builtin_amdgcn_raw_buffer_load_b128(b3_rsrc(sa), o + 16u * v, 0, 0));
+        }
+#pragma unroll
+        for (int j = 0; j < RT; ++j) {
+            const uint32_t o = ((uint32_t)(16 * j + rl) * sb.ld4 + (uint32_t)k * (uint32_t)EB) | (inv << 31);
+            fb[p][j] = __builtin_bit_cast(uint4, __builtin_amdgcn_raw_buffer_load_b128(b3_rsrc(sb), o, 0, 0));
+        }
+    };
+    auto mma = [&](int p) {
+        if constexpr (BF) {
+            bf8v av[RT];
+#pragma unroll
+            for (int i = 0; i < RT; ++i) {
+                if constexpr (AV == 2) {
+                    const float4 x0 = __builtin_bit_cast(float4, fa[p][i][0]), x1 = __builtin_bit_cast(float4, fa[p][i][1]);
+                    av[i] = __builtin_bit_cast(bf8v, make_uint4(cvt_pk_bf16(x0.x, x0.y), cvt_pk_bf16(x0.z, x0.w),
+                                                                cvt_pk_bf16(x1.x, x1.y), cvt_pk_bf16(x1.z, x1.w)));
+                } else {
+                    av[i] = __builtin_bit_cast(bf8v, fa[p][i][0]);
+                }
+            }
+#pragma unroll
+            for (int i = 0; i < RT; ++i)
+#pragma unroll
+                for (int j = 0; j < RT; ++j)
+                    acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(av[i], __builtin_bit_cast(bf8v, fb[p][j]), acc[i][j], 0, 0, 0);
+        } else {
+#pragma unroll
+            for (int q = 0; q < 4; ++q)
+#pragma unroll
+                for (int i = 0; i < RT; ++i)
+#pragma unroll
+                    for (int j = 0; j < RT; ++j)
+                        acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x4f32(__builtin_bit_cast(f4, fa[p][i][0])[q],
+                                                                         __builtin_bit_cast(f4, fb[p][j])[q], acc[i][j], 0, 0, 0);
+        }
+    };
+    // the wave's blocks q = 0, 1, ... are the contraction's wave + 8 q; register set q % PD
+    const int nblk = (Kv + BK - 1) / BK;
+    const int nq = nblk > wave ? (nblk - wave + KS_WAVES - 1) / KS_WAVES : 0;
+#pragma unroll
+    for (int p = 0; p < PD; ++p) load(p, wave + KS_WAVES * p);
+    for (int q0 = 0; q0 < nq; q0 += PD)
+#pragma unroll
+        for (int p = 0; p < PD; ++p) {
+            if (q0 + p >= nq) break;
+            mma(p);
+            load(p, wave + KS_WAVES * (q0 + p + PD));  // (past the contraction: zeros, unused)
+        }
+    // lane: rows 16 i + 4 kg + r, column 16 j + rl of the tile
+#pragma unroll
+    for (int i = 0; i < RT; ++i)
+#pragma unroll
+        for (int j = 0; j < RT; ++j)
+#pragma unroll
+            for (int r = 0; r < 4; ++r) part[wave][(16 * i + 4 * kg + r) * LD + 16 * j + rl] = acc[i][j][r];
+    __syncthreads();
+    for (int e = tid; e < TS * TS; e += KS_THREADS) {
+        const int mr = e / TS, nr = e % TS, m = m0 + mr, n = n0 + nr;
+        float p[KS_WAVES];
+#pragma unroll
+        for (int w = 0; w < KS_WAVES; ++w) p[w] = part[w][mr * LD + nr];
+        const float v = ((p[0] + p[1]) + (p[2] + p[3])) + ((p[4] + p[5]) + (p[6] + p[7]));
+        if (m < Mv && n < Nv)
+            ((TO*)g.c)[(size_t)bz * g.c_z + (size_t)m * g.c_ld + n] =
+                from_f<TO>(act_fn(g.act, v + g.bias[(size_t)cn * g.bias_z + n]));
     }
 }
 
@@ -1985,7 +2107,7 @@ __global__ __launch_bounds__(B3_THREADS) void upd128x3_kernel(GemmArgs g) {
 // ------------------------------------------------------------------------------------
 // Output layer, one wavefront per sample row: z = W x + b over <= 16 outputs, the output
 // activation (eq. (3), softmax eq. (5)), then either the output error (training, eq. (9)
-// or (10)) or the predicted class and the correct count (inference).
+// or (10)).  (Inference: infer_out_kernel below.)
 
 struct RowArgs {
     const void* x;  // input activations: xrows (data set) or workspace [z][rows][ld]
@@ -2009,7 +2131,7 @@ struct RowArgs {
     double* cost;      // inference: [rows] cost of each data-set row (nullable; needs y)
 };
 
-template <typename TX, typename TW, typename TD, bool TRAIN>
+template <typename TX, typename TW, typename TD>
 __global__ __launch_bounds__(256) void out_layer_kernel(RowArgs a) {
     const int lane = threadIdx.x & 63;
     const int row = blockIdx.x * 4 + (threadIdx.x >> 6);
@@ -2049,49 +2171,112 @@ __global__ __launch_bounds__(256) void out_layer_kernel(RowArgs a) {
 #pragma unroll
         for (int o = 0; o < MAX_OUT; ++o) xo[o] = act_fn(a.act, zo[o]);
     }
-    if constexpr (TRAIN) {
-        const int label = a.y[drow];
-        TD* d = (TD*)a.delta + (size_t)z * a.d_z + (size_t)row * a.O;
-        if (lane < a.O) {
-            float xv = 0.f;
+    const int label = a.y[drow];
+    TD* d = (TD*)a.delta + (size_t)z * a.d_z + (size_t)row * a.O;
+    if (lane < a.O) {
+        float xv = 0.f;
 #pragma unroll
-            for (int o = 0; o < MAX_OUT; ++o) if (o == lane) xv = xo[o];
-            const float e = (lane == label) ? 1.0f : 0.0f;
-            const float dv = (a.loss == LOSS_XENT) ? (xv - e) : (xv - e) * act_deriv(a.act, xv);
-            d[lane] = from_f<TD>(dv);
-        }
-    } else {
-        int best = 0;
-        float bv = xo[0];
+        for (int o = 0; o < MAX_OUT; ++o) if (o == lane) xv = xo[o];
+        const float e = (lane == label) ? 1.0f : 0.0f;
+        const float dv = (a.loss == LOSS_XENT) ? (xv - e) : (xv - e) * act_deriv(a.act, xv);
+        d[lane] = from_f<TD>(dv);
+    }
+}
+
+// The output layer of an inference: 16 rows per workgroup, z = X W^T + b on v_mfma_f32_16x16x4_f32
+// with the outputs padded to 16 (the four waves split H in blocks of 16, loaded 16 or 8 bytes a lane
+// in the instruction's layout; their partial tiles are added in LDS in wave order), then one lane per
+// (row, output): activation, argmax, cost and count by reductions over the 16 lanes of a row.
+// Bound: the read of the hidden activations.  (One wavefront per row, each lane adding up to 16
+// outputs and reducing every one over the wave, took 79 us for 8,192 rows of 1,024, 0.4 TB/s.)
+template <typename TX, typename TW>
+__global__ __launch_bounds__(256) void infer_out_kernel(RowArgs a) {
+    __shared__ float part[4][16][17];
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, l16 = lane & 15, g = lane >> 4;
+    const int row0 = blockIdx.x * 16;
+    const int64_t v = a.n_total - a.r0;
+    const int valid = (int)(v > a.step_rows ? a.step_rows : v);  // (the rows of this chunk)
+    {
+        const int r = min(row0 + l16, valid - 1);
+        const TX* x = (const TX*)a.x + (size_t)(a.x_xrows ? a.r0 + r : r) * a.x_ld;
+        const TW* W = (const TW*)a.w + (size_t)min(l16, a.O - 1) * a.H;
+        constexpr int PF = 4;  // blocks in flight, each with a chain of sums of its own
+        f4 acc[PF];
 #pragma unroll
-        for (int o = 1; o < MAX_OUT; ++o) if (o < a.O && xo[o] > bv) { bv = xo[o]; best = o; }
-        if (lane == 0) {
-            if (a.pred) a.pred[drow] = best;
-            if (a.correct && a.y && a.y[drow] == best) atomicAdd(a.correct, 1ull);
-            if (a.cost && a.y) {
-                // the cost whose output error training uses: quadratic 1/2 sum (x - e)^2, or
-                // cross-entropy (eq. (6) for a softmax output, the two-class form per output
-                // for a sigmoid output), in double from the fp32 outputs
-                const int label = a.y[drow];
-                double c = 0.0;
+        for (int p = 0; p < PF; ++p) acc[p] = f4{0.f, 0.f, 0.f, 0.f};
+        // a block of 16 along H: this lane's four values of the row and of the output's weights
+        // (past H: the row's first values against zero weights)
+        auto load = [&](int h0, float4& xv, float4& wv) {
+            const int h = h0 + 4 * g;
+            const bool ok = h < a.H;
+            xv = load4(x + (ok ? h : 0));
+            wv = load4(W + (ok ? h : 0));
+            if (!ok || l16 >= a.O) wv = make_float4(0.f, 0.f, 0.f, 0.f);
+            if (!ok) xv = make_float4(0.f, 0.f, 0.f, 0.f);
+            if constexpr (sizeof(TW) == 2 && sizeof(TX) == 4)  // bf16 operand
+                xv = make_float4(bf2f(f2bf(xv.x)), bf2f(f2bf(xv.y)), bf2f(f2bf(xv.z)), bf2f(f2bf(xv.w)));
+        };
+        for (int h0 = wave * 16; h0 < a.H; h0 += 64 * PF) {
+            float4 xv[PF], wv[PF];
 #pragma unroll
-                for (int o = 0; o < MAX_OUT; ++o) {
-                    if (o >= a.O) continue;
-                    const double x = (double)xo[o], e = (o == label) ? 1.0 : 0.0;
-                    if (a.loss != LOSS_XENT) c += 0.5 * (x - e) * (x - e);
-                    else if (a.act == ACT_SOFTMAX) c += (o == label) ? -log(x) : 0.0;
-                    else c += -(e * log(x) + (1.0 - e) * log(1.0 - x));
-                }
-                a.cost[drow] = c;
+            for (int p = 0; p < PF; ++p) load(h0 + 64 * p, xv[p], wv[p]);
+#pragma unroll
+            for (int p = 0; p < PF; ++p) {
+                acc[p] = __builtin_amdgcn_mfma_f32_16x16x4f32(xv[p].x, wv[p].x, acc[p], 0, 0, 0);
+                acc[p] = __builtin_amdgcn_mfma_f32_16x16x4f32(xv[p].y, wv[p].y, acc[p], 0, 0, 0);
+                acc[p] = __builtin_amdgcn_mfma_f32_16x16x4f32(xv[p].z, wv[p].z, acc[p], 0, 0, 0);
+                acc[p] = __builtin_amdgcn_mfma_f32_16x16x4f32(xv[p].w, wv[p].w, acc[p], 0, 0, 0);
             }
         }
-        if (a.out && lane < a.O) {
-            float xv = 0.f;
 #pragma unroll
-            for (int o = 0; o < MAX_OUT; ++o) if (o == lane) xv = xo[o];
-            a.out[(size_t)drow * a.O + lane] = xv;
-        }
+        for (int i = 0; i < 4; ++i) part[wave][4 * g + i][l16] = (acc[0][i] + acc[1][i]) + (acc[2][i] + acc[3][i]);
     }
+    __syncthreads();
+    const int rr = tid >> 4, o = tid & 15, row = row0 + rr;
+    const bool live = row < valid && o < a.O;
+    const int64_t drow = a.r0 + row;
+    const float z = (part[0][rr][o] + part[1][rr][o]) + (part[2][rr][o] + part[3][rr][o]) + (o < a.O ? a.bias[o] : 0.f);
+    float xo;
+    if (a.act == ACT_SOFTMAX) {
+        const float m = row_allmax16(o < a.O ? z : -INFINITY);
+        const float e = o < a.O ? expf(z - m) : 0.f;
+        xo = e * (1.0f / row_allsum16(e));
+    } else {
+        xo = act_fn(a.act, z);
+    }
+    // argmax, the lowest index on ties; a NaN is never greater (only as the first output it stays)
+    float bv = o >= a.O || (o > 0 && xo != xo) ? -INFINITY : xo;
+    int best = o < a.O ? o : MAX_OUT;
+    const bool first_nan = __shfl(xo != xo ? 1 : 0, lane & 48) != 0;
+#pragma unroll
+    for (int sh = 1; sh < 16; sh <<= 1) {
+        const float ov = __shfl_xor(bv, sh, 16);
+        const int oi = __shfl_xor(best, sh, 16);
+        if (ov > bv || (ov == bv && oi < best)) { bv = ov; best = oi; }
+    }
+    if (first_nan) best = 0;
+    const int label = a.y && row < valid ? a.y[drow] : -1;
+    if (a.correct && a.y) {
+        const unsigned long long hit = __ballot(o == 0 && row < valid && label == best);
+        if (lane == 0 && hit) atomicAdd(a.correct, (unsigned long long)__popcll(hit));
+    }
+    if (a.cost && a.y) {
+        // the cost whose output error training uses: quadratic 1/2 sum (x - e)^2, or cross-entropy
+        // (eq. (6) for a softmax output, the two-class form per output for a sigmoid output), in
+        // double from the fp32 outputs
+        double c = 0.0;
+        if (live) {
+            const double x = (double)xo, e = (o == label) ? 1.0 : 0.0;
+            if (a.loss != LOSS_XENT) c = 0.5 * (x - e) * (x - e);
+            else if (a.act == ACT_SOFTMAX) c = (o == label) ? -log(x) : 0.0;
+            else c = -(e * log(x) + (1.0 - e) * log(1.0 - x));
+        }
+#pragma unroll
+        for (int sh = 1; sh < 16; sh <<= 1) c += __shfl_xor(c, sh, 16);
+        if (o == 0 && row < valid) a.cost[drow] = c;
+    }
+    if (o == 0 && row < valid && a.pred) a.pred[drow] = best;
+    if (live && a.out) a.out[(size_t)drow * a.O + o] = xo;
 }
 
 // ------------------------------------------------------------------------------------
@@ -2194,40 +2379,6 @@ __global__ __launch_bounds__(256) void upd_small_kernel(UpdSmallArgs a) {
 }
 
 // ------------------------------------------------------------------------------------
-// Forward layer split along the contraction (few, long-contraction tiles): the partial
-// products of the ksplit slices are summed here, then the bias and the activation
-// (eq. (2)-(3)):  out[z][r][c] = phi(sum_s part[s][z][r][c] + b[c]).  Thread per (r, c).
-
-struct FwdReduceArgs {
-    const float* part;  // [ksplit][K][rows][N]
-    int64_t split;      // K * rows * N
-    int ksplit;
-    float* out;         // [K][rows][N]
-    const float* bias;  // b (+ z * bias_z)
-    int64_t bias_z;
-    int N, act;
-    int64_t n_total;
-    int k_rep;
-    int64_t r0;
-    int step_rows;
-};
-
-__global__ __launch_bounds__(256) void fwd_reduce_kernel(FwdReduceArgs a) {
-    const int c = blockIdx.x * 256 + threadIdx.x;
-    const int r = blockIdx.y, z = blockIdx.z;
-    int64_t v = shard_len(a.n_total, a.k_rep, z) - a.r0;
-    const int valid = (int)(v < 0 ? 0 : (v > a.step_rows ? a.step_rows : v));
-    if (r >= valid || c >= a.N) return;
-    const size_t e = ((size_t)z * a.step_rows + r) * a.N + c;
-    float sum = 0.f;
-    for (int sl = 0; sl < a.ksplit; ++sl) sum += a.part[(size_t)sl * a.split + e];
-    a.out[e] = act_fn(a.act, sum + a.bias[(size_t)z * a.bias_z + c]);
-}
-
-// ------------------------------------------------------------------------------------
-__device__ inline float row_allmax16(float v);
-__device__ inline float row_allsum16(float v);
-
 // Output activation and output error of one (row, output) lane, the 16 lanes of a row taking
 // part together (softmax over them): eq. (3) / (5) and (9) / (10); zero on dead lanes (rows
 // past the step or outputs past O); rounded to the error type TD.
@@ -4363,15 +4514,21 @@ __global__ __launch_bounds__(256) void gather_rows_kernel(const float* x, const 
     if (threadIdx.x == 0) yo[r] = y[src];
 }
 
-// sum of n doubles in a fixed order (thread t takes t, t + 256, ...; then a fixed tree)
-__global__ __launch_bounds__(256) void sum_f64_kernel(const double* v, int64_t n, double* out) {
-    __shared__ double part[256];
+// sum of n doubles in a fixed order (thread t takes t, t + 1024, ... in eight chains; then a fixed
+// tree).  Bound: load latency, so eight loads in flight a thread (10,000 costs: 14.5 us with 256
+// threads of one chain each).
+constexpr int SUM_THREADS = 1024;
+__global__ __launch_bounds__(SUM_THREADS) void sum_f64_kernel(const double* v, int64_t n, double* out) {
+    __shared__ double part[SUM_THREADS];
     const int t = threadIdx.x;
-    double s = 0.0;
-    for (int64_t i = t; i < n; i += 256) s += v[i];
-    part[t] = s;
+    double s[8] = {0.0, 0.0, 0.0, 0.0, 0.0, 0.0, 0.0, 0.0};
+    for (int64_t i = t; i < n; i += 8 * SUM_THREADS)
+#pragma unroll
+        for (int u = 0; u < 8; ++u)
+            if (i + u * SUM_THREADS < n) s[u] += v[i + u * SUM_THREADS];
+    part[t] = ((s[0] + s[1]) + (s[2] + s[3])) + ((s[4] + s[5]) + (s[6] + s[7]));
     __syncthreads();
-    for (int h = 128; h > 0; h >>= 1) {
+    for (int h = SUM_THREADS / 2; h > 0; h >>= 1) {
         if (t < h) part[t] += part[t + h];
         __syncthreads();
     }

@@ -317,6 +317,20 @@ const char* x3_name(const char* name) {
     return name;
 }
 
+// Tile (in units of 16) of gemm_ks_kernel for an M x N forward product over Z CNs, or 0 where the
+// other kernels are the better ones.  The tiles of 64, 128 or 256 cost the time of one long walk
+// along k (us, 784-long: gemm_kernel and gemm_kw_kernel 14-25, gemm128x3 37, gemm256x3 56) until
+// they fill the CUs; this kernel 8 at first and then 22 (fp32) or 15-20 (bf16) per 1,000 tiles of
+// 32 x 32.  Measured, this kernel / the other: fp32 128 x 256, K = 1 8 / 56, K = 32 (1,024 tiles)
+// 28 / 58, K = 64 (2,048) 46 / 61, but 128 x 128, K = 128 (2,048) 53 / 47; bf16 50 x 256, K = 16
+// (256) 11 / 13, 50 x 512, K = 16 (512) 14 / 15, K = 32 23 / 18; bf16 128 x 512, K = 16 (1,024)
+// 21 / 25, K = 32 36 / 31.
+int ks_tile(bool bf16, int M, int N, int64_t Z) {
+    auto tiles = [&](int t) { return (int64_t)((M + t - 1) / t) * ((N + t - 1) / t) * Z; };
+    if (tiles(32) > (!bf16 ? 1536 : M <= 64 ? 512 : 1024)) return 0;
+    return tiles(16) <= 256 ? 1 : 2;
+}
+
 template <bool BF, typename TA, typename TB, bool A_KC, bool B_KC, int EPI, typename TO>
 pnn_status run_gemm(pnn_net* n, hipStream_t s, const GemmArgs& g, int Z, const char* name) {
     // shapes the kernel assumes: 16-byte loads along contiguous dimensions
@@ -332,15 +346,32 @@ pnn_status run_gemm(pnn_net* n, hipStream_t s, const GemmArgs& g, int Z, const c
     if ((!A_KC && (g.sample_dims & 1)) || (!B_KC && (g.sample_dims & 2)) || ((A_KC || B_KC) && (g.sample_dims & 4)))
         return fail(n, PNN_EINVAL, "%s: vector loads along a sample dimension", name);
     dim3 grid((g.N + 63) / 64, (g.M + 63) / 64, (unsigned)(Z * g.ksplit));
+    if constexpr (A_KC && B_KC && EPI == EPI_FWD && (BF ? sizeof(TB) == 2 : sizeof(TB) == 4)) {
+        const int ks = g.zpart == nullptr && g.ksplit == 1 && !(g.sample_dims & 4) && g.Kd % vec == 0 ? ks_tile(BF, g.M, g.N, Z) : 0;
+        const int64_t rows = (int64_t)(g.M + 16 * ks - 1) / std::max(16 * ks, 1);
+        if (ks > 0 && rows > 0 && rows <= 65535 && Z <= 65535) {
+            const dim3 gk((g.N + 16 * ks - 1) / (16 * ks), (unsigned)rows, (unsigned)Z);
+            Launch l(n, s, name);
+            if (ks == 1) gemm_ks_kernel<BF, TA, TO, 1><<<gk, KS_THREADS, 0, s>>>(g);
+            else gemm_ks_kernel<BF, TA, TO, 2><<<gk, KS_THREADS, 0, s>>>(g);
+            return l.done();
+        }
+    }
     if (grid.x == 0 || grid.y == 0 || grid.z == 0 || grid.y > 65535 || grid.z > 65535)
         return fail(n, PNN_EINVAL, "%s: bad grid %u x %u x %u", name, grid.x, grid.y, grid.z);
     if constexpr (!BF) {
         const dim3 g128((g.N + 127) / 128, (g.M + 127) / 128, (unsigned)(Z * g.ksplit));
+        bool few = false;  // an update with few strips
         // the weight update over at most 128 samples of a layer of >= 128 neurons: strips of 128
         // rows of W on the bf16 matrix cores (upd128x3_kernel)
         if constexpr (EPI == EPI_UPD && !A_KC && !B_KC) {
             const int kmax = (g.sample_dims & 4) ? g.step_rows : g.Kd;
-            if (n->gemm_x3 && g.M >= 128 && g.N >= 128 && kmax <= U3_KMAX && g.ksplit == 1 && g.shadow == nullptr &&
+            // (a workgroup walks all columns of its strip, 35 to 45 us for 784 however few strips there
+            // are; the 64 x 64 tiles of gemm_kernel are faster up to 128 strips -- 784-256-10, B = 100,
+            // strips / tiles in us: K = 4 46 / 14, K = 32 48 / 28, K = 64 (128 strips) 50 / 46,
+            // K = 128 62 / 78)
+            few = (int64_t)((g.M + 127) / 128) * Z <= 128 && kmax <= U3_KMAX && g.dout == nullptr;
+            if (n->gemm_x3 && g.M >= 128 && g.N >= 128 && !few && kmax <= U3_KMAX && g.ksplit == 1 && g.shadow == nullptr &&
                 g.N % 4 == 0 && g.c_ld % 4 == 0) {
                 static const hipError_t attr =
                     hipFuncSetAttribute((const void*)upd128x3_kernel<false>, hipFuncAttributeMaxDynamicSharedMemorySize,
@@ -362,7 +393,12 @@ pnn_status run_gemm(pnn_net* n, hipStream_t s, const GemmArgs& g, int Z, const c
         // large fp32 shapes with both operands along k and at least 256 columns: 128 x 256 tiles
         // (gemm256x3_kernel)
         if constexpr (A_KC && B_KC && (EPI == EPI_FWD || EPI == EPI_STORE)) {
-            if (n->gemm_x3 && g.M >= 128 && g.N >= 256 && g.shadow == nullptr && g.ksplit == 1 && !(g.sample_dims & 4)) {
+            // (not where its tiles leave a last round of workgroups emptier than the 128 x 128 tiles,
+            // whose round takes 0.66 of the time: 1,808 rows x 1,024 on 256 CUs 67 -> 45 us)
+            const int64_t t256 = (int64_t)((g.N + 255) / 256) * ((g.M + 127) / 128) * Z;
+            const int64_t t128 = (int64_t)((g.N + 127) / 128) * ((g.M + 127) / 128) * Z;
+            const bool fuller = g.zpart != nullptr || (t256 + 255) / 256 <= 0.66 * (double)((t128 + 255) / 256);
+            if (n->gemm_x3 && g.M >= 128 && g.N >= 256 && fuller && g.shadow == nullptr && g.ksplit == 1 && !(g.sample_dims & 4)) {
                 static const hipError_t attr = hipFuncSetAttribute((const void*)gemm256x3_kernel<EPI>,
                                                                    hipFuncAttributeMaxDynamicSharedMemorySize,
                                                                    (int)g2_lds_bytes());
@@ -376,7 +412,7 @@ pnn_status run_gemm(pnn_net* n, hipStream_t s, const GemmArgs& g, int Z, const c
             return fail(n, PNN_EINVAL, "%s: the fused last layer needs the split-bf16 kernels for this shape", name);
         // other large fp32 shapes: 128 x 128 tiles on the bf16 matrix cores, each fp32 operand
         // split into three bf16 parts (gemm128x3_kernel)
-        if (n->gemm_x3 && g.M >= 128 && g.N >= 128 && g.shadow == nullptr && (g.ksplit == 1 || g.kchunk % B3_BK == 0)) {
+        if (n->gemm_x3 && g.M >= 128 && g.N >= 128 && !few && g.shadow == nullptr && (g.ksplit == 1 || g.kchunk % B3_BK == 0)) {
             static const hipError_t attr = hipFuncSetAttribute((const void*)gemm128x3_kernel<A_KC, B_KC, EPI>,
                                                                hipFuncAttributeMaxDynamicSharedMemorySize,
                                                                (int)b3_lds_bytes());
@@ -442,23 +478,6 @@ pnn_status minibatch_step(pnn_net* n, const float* X, const int32_t* Y, int64_t 
         g.c = n->act_ws[l]; g.c_z = (int64_t)B * n->sizes[l]; g.c_ld = n->sizes[l];
         g.bias = n->theta + n->off_b[l - 1]; g.bias_z = ps;
         g.act = n->act[l - 1];
-        if (!BF && l == 1 && n->ksplit > 1) {
-            // few tiles with a long contraction: split it, then sum, bias and activation
-            g.c = n->ppart; g.ksplit = n->ksplit; g.kchunk = n->kchunk;
-            g.c_split = (int64_t)K * B * n->sizes[1];
-            TRY((run_gemm<false, float, float, true, true, EPI_STORE, float>(n, s, g, K, "fwd_gemm")));
-            FwdReduceArgs ra;
-            memset(&ra, 0, sizeof ra);
-            ra.part = n->ppart; ra.split = g.c_split; ra.ksplit = n->ksplit;
-            ra.out = (float*)n->act_ws[1];
-            ra.bias = n->theta + n->off_b[0]; ra.bias_z = ps;
-            ra.N = n->sizes[1]; ra.act = n->act[0];
-            ra.n_total = N; ra.k_rep = K; ra.r0 = r0; ra.step_rows = B;
-            Launch lr(n, s, "fwd_reduce");
-            fwd_reduce_kernel<<<dim3((n->sizes[1] + 255) / 256, B, K), 256, 0, s>>>(ra);
-            TRY(lr.done());
-            continue;
-        }
         if (fx3) {
             g.w2 = n->theta + n->off_w[1]; g.w2_z = ps;
             g.zpart = n->fx3_zpart; g.o2 = n->sizes[2];
@@ -527,8 +546,8 @@ pnn_status minibatch_step(pnn_net* n, const float* X, const int32_t* Y, int64_t 
         a.delta = n->del_ws[L]; a.d_z = (int64_t)B * n->sizes[L];
         dim3 grid((B + 3) / 4, 1, K);
         Launch lc(n, s, "out_layer");
-        if (L == 1) out_layer_kernel<float, TH, TH, true><<<grid, 256, 0, s>>>(a);
-        else out_layer_kernel<TH, TH, TH, true><<<grid, 256, 0, s>>>(a);
+        if (L == 1) out_layer_kernel<float, TH, TH><<<grid, 256, 0, s>>>(a);
+        else out_layer_kernel<TH, TH, TH><<<grid, 256, 0, s>>>(a);
         TRY(lc.done());
     }
     // hidden errors, back to front, with the pre-update weights (eq. (11))
@@ -1161,17 +1180,6 @@ pnn_status pnn_init(const pnn_config* cfg, const float* theta0_host, void* hip_s
             if (l < n->L && (st = dev_alloc(n, (char**)&n->act_ws[l], cnt)) != PNN_OK) return bail(st);
             if ((st = dev_alloc(n, (char**)&n->del_ws[l], cnt)) != PNN_OK) return bail(st);
         }
-        // fp32, first layer with few output tiles (less than one workgroup per CU) and the
-        // 784-long contraction: split the contraction into slices of 112
-        if (!n->bf16 && n->L >= 2) {
-            const int N1 = n->sizes[1], In = n->sizes[0];
-            const int64_t wgs = (int64_t)((N1 + 63) / 64) * ((B + 63) / 64) * K;
-            if (!(B >= 128 && N1 >= 128) && wgs < 256 && In >= 256) {
-                n->kchunk = (int)round_up((In + 7) / 8, 16);
-                n->ksplit = (In + n->kchunk - 1) / n->kchunk;
-                if ((st = dev_alloc(n, &n->ppart, (size_t)n->ksplit * K * B * N1)) != PNN_OK) return bail(st);
-            }
-        }
         // persistent mini-batch plan: one hidden layer, batches of at most 64 rows, at most 16
         // outputs, and every CN's ceil(H / 16 rt) tile workgroups co-resident (rt = 1, or 2 when
         // 16-neuron tiles do not fit); PNN_MB_PLAN=launch selects the per-layer launches
@@ -1229,7 +1237,7 @@ pnn_status pnn_init(const pnn_config* cfg, const float* theta0_host, void* hip_s
         // upd128x3_kernel forms the hidden errors and updates W2 and b2 (no pass over the
         // hidden layer's activations and errors of its own); PNN_MB_PLAN=launch keeps the
         // separate last-layer kernel
-        if (!forced_launch && !n->mbp && !n->bf16 && n->gemm_x3 && n->L == 2 && B == 128 && n->ksplit == 1 &&
+        if (!forced_launch && !n->mbp && !n->bf16 && n->gemm_x3 && n->L == 2 && B == 128 &&
             n->sizes[1] >= 256 && n->sizes[1] % 4 == 0 && n->sizes[2] <= MAX_OUT && n->sizes[0] >= 128 &&
             n->sizes[0] % 4 == 0 && n->off_w[1] % 4 == 0 && n->off_b[1] % 4 == 0 && n->pstride % 4 == 0) {
             const size_t ntile = (size_t)(n->sizes[1] + 255) / 256;
@@ -1440,15 +1448,15 @@ static pnn_status run_inference(pnn_net* n, int32_t which, const float* x_dev, i
         a.y = y_dev; a.out = out_dev; a.pred = pred_dev; a.correct = count ? correct : nullptr;
         a.cost = cost;
         const int rws = (int)std::min<int64_t>(CH, nrows - r0);
-        dim3 grid((rws + 3) / 4, 1, 1);
+        dim3 grid((rws + 15) / 16, 1, 1);
         Launch lc(n, s, "infer_out");
         if (n->bf16) {
             a.w = sh + n->off_w[L - 1];
-            if (L == 1) out_layer_kernel<float, bf16_t, float, false><<<grid, 256, 0, s>>>(a);
-            else out_layer_kernel<bf16_t, bf16_t, float, false><<<grid, 256, 0, s>>>(a);
+            if (L == 1) infer_out_kernel<float, bf16_t><<<grid, 256, 0, s>>>(a);
+            else infer_out_kernel<bf16_t, bf16_t><<<grid, 256, 0, s>>>(a);
         } else {
             a.w = th + n->off_w[L - 1];
-            out_layer_kernel<float, float, float, false><<<grid, 256, 0, s>>>(a);
+            infer_out_kernel<float, float><<<grid, 256, 0, s>>>(a);
         }
         TRY(lc.done());
     }
@@ -1464,7 +1472,7 @@ static pnn_status eval_run(pnn_net* n, int32_t which, const float* x_dev, const 
                       cost_host ? cost : nullptr, ws, correct, s));
     if (cost_host) {
         Launch lc(n, s, "eval_cost_sum");
-        sum_f64_kernel<<<1, 256, 0, s>>>(cost, nrows, cost_sum);
+        sum_f64_kernel<<<1, SUM_THREADS, 0, s>>>(cost, nrows, cost_sum);
         TRY(lc.done());
     }
     unsigned long long c = 0;

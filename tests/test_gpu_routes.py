@@ -162,3 +162,85 @@ def test_persistent_mini_batch_gives_up_waiting(monkeypatch):
             net.get_params(0)
         assert ei.value.status == B.PNN_EHIP and "timed out" in str(ei.value)
         net.close()
+
+
+# ------------------------------------------------------------------------------------
+# forward products with the contraction split over the waves of a workgroup (tiles of 16 and of
+# 32), the update in 64 x 64 tiles where there are few strips, and the inference output layer:
+# rows and widths at the edges of their tiles, contractions of 1 to 52 blocks
+
+@pytest.mark.parametrize("precision", [I.FP32, I.BF16_MIXED])
+@pytest.mark.parametrize("over,N", [
+    (dict(sizes=(784, 136, 10), batch=100, replicas=2), 2 * 150 + 1),
+    (dict(sizes=(784, 256, 10), batch=129, replicas=3), 3 * 140 + 2),
+    (dict(sizes=(784, 200, 104, 10), acts=(I.TANH, I.SIGMOID, I.SIGMOID), batch=70, replicas=3), 3 * 100 + 1),
+    (dict(sizes=(8, 24, 16, 2), acts=(I.TANH, I.SIGMOID, I.SIGMOID), batch=65, replicas=2), 2 * 70 + 1),
+    (dict(sizes=(784, 256, 10), batch=100, replicas=72), 72 * 100 + 3),   # 32 x 32 tiles beyond the rule
+])
+def test_split_forward_and_few_strips(over, N, precision, monkeypatch):
+    monkeypatch.setenv("PNN_MB_PLAN", "launch")
+    train_both(I.WORKLOADS[2].scaled(precision=precision, **over), N, 1).close()
+
+
+@pytest.mark.parametrize("precision", [I.FP32, I.BF16_MIXED])
+@pytest.mark.parametrize("sizes,acts,loss,rows", [
+    ((784, 128, 10), (I.SIGMOID, I.SIGMOID), I.LOSS_MSE, 1),
+    ((784, 40, 10), (I.RELU, I.SOFTMAX), I.LOSS_XENT, 17),
+    ((784, 264, 16), (I.TANH, I.SOFTMAX), I.LOSS_XENT, 300),
+    ((784, 1024, 10), (I.SIGMOID, I.SIGMOID), I.LOSS_XENT, 1809),
+    ((784, 512, 256, 3), (I.RELU, I.LEAKY_RELU, I.SIGMOID), I.LOSS_MSE, 8192 + 33),  # two chunks
+    ((784, 1), (I.SIGMOID,), I.LOSS_XENT, 50),
+    ((784, 10), (I.SOFTMAX,), I.LOSS_XENT, 33),
+    ((24, 8, 2), (I.TANH, I.SIGMOID), I.LOSS_MSE, 15),
+])
+def test_inference_routes(sizes, acts, loss, rows, precision):
+    """Outputs, predictions, count and cost of one CN against the oracle's forward of the same
+    parameters (fp32 1e-5, the one-step bar; bf16 2e-2)."""
+    w = I.WORKLOADS[2].scaled(sizes=sizes, acts=acts, loss=loss, precision=precision, replicas=2, batch=8)
+    X, _ = I.random_batch(sizes[0], sizes[-1], rows, 3)
+    y = np.random.default_rng(4).integers(0, sizes[-1], rows).astype(np.int32)
+    th = I.random_params(sizes, 9, 0.1)
+    log(f"{sizes} rows {rows} precision {precision}")
+    net = make_net(w, I.init_params(w))
+    net.set_params(1, th)
+    pred = torch.full((rows,), -1, dtype=torch.int32, device="cuda")
+    out = torch.empty((rows, sizes[-1]), dtype=torch.float32, device="cuda")
+    correct = net.infer(dev(X), pred, which=1, out=out, y=dev(y), count=True)
+    got, p = out.cpu().numpy(), pred.cpu().numpy()
+    o = O.Oracle.from_workload(w)
+    ref = o.forward(th.astype(np.float64), X)
+    tol = 1e-5 if precision == I.FP32 else 2e-2
+    assert np.max(np.abs(got - ref)) <= tol
+    assert np.array_equal(p, np.argmax(got, axis=1))   # (of its own outputs: lowest index on ties)
+    assert correct == int(np.sum(p == y))
+    c, cost = net.evaluate(dev(X), dev(y), which=1)
+    c2, cost2 = net.evaluate_noalloc(dev(X), dev(y), which=1)
+    g64 = got.astype(np.float64)
+    hot = np.eye(sizes[-1])[y]
+    if loss == I.LOSS_MSE:
+        want = 0.5 * np.sum((g64 - hot) ** 2, axis=1)
+    elif acts[-1] == I.SOFTMAX:
+        want = -np.log(np.sum(g64 * hot, axis=1))
+    else:
+        want = -np.sum(hot * np.log(g64) + (1 - hot) * np.log(1 - g64), axis=1)
+    assert (c, c2) == (correct, correct) and abs(cost - want.mean()) <= 1e-12 * max(1, rows) and cost2 == cost
+    net.close()
+
+
+def test_inference_of_not_a_number():
+    """A NaN output is never the greatest one, unless it is the first: the prediction of a row
+    without any number is 0, and other rows are not touched."""
+    w = I.WORKLOADS[2].scaled(sizes=(784, 16, 10), replicas=1, batch=8)
+    X, _ = I.random_batch(784, 10, 40, 3)
+    net = make_net(w, I.init_params(w))
+    pred = torch.empty(40, dtype=torch.int32, device="cuda")
+    out = torch.empty((40, 10), dtype=torch.float32, device="cuda")
+    net.infer(dev(X), pred, out=out)
+    clean, ref = out.cpu().numpy(), pred.cpu().numpy()
+    X[7] = np.nan
+    net.infer(dev(X), pred, out=out)
+    got, p = out.cpu().numpy(), pred.cpu().numpy()
+    rest = np.arange(40) != 7
+    assert np.all(np.isnan(got[7])) and p[7] == 0
+    assert np.array_equal(got[rest], clean[rest]) and np.array_equal(p[rest], ref[rest])
+    net.close()
