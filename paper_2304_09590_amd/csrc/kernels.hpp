@@ -2105,9 +2105,41 @@ __global__ __launch_bounds__(B3_THREADS) void upd128x3_kernel(GemmArgs g) {
 }
 
 // ------------------------------------------------------------------------------------
-// Output layer, one wavefront per sample row: z = W x + b over <= 16 outputs, the output
-// activation (eq. (3), softmax eq. (5)), then either the output error (training, eq. (9)
-// or (10)).  (Inference: infer_out_kernel below.)
+// Output activation and output error of one (row, output) lane, the 16 lanes of a row taking
+// part together (softmax over them): eq. (3) / (5) and (9) / (10); zero on dead lanes (rows
+// past the step or outputs past O); rounded to the error type TD.
+
+// DPP: the row reductions by DPP instead of shuffles through LDS (another order of the sum; the
+// whole wave active).
+template <typename TD, bool DPP = false>
+__device__ inline float out_error(float zv, bool live, int o, int label, int act_out, int loss) {
+    float xo;
+    if (DPP && act_out == ACT_SOFTMAX) {
+        const float m = row_allmax16(live ? zv : -INFINITY);
+        const float ex = live ? expf(zv - m) : 0.f;
+        xo = ex * (1.0f / row_allsum16(ex));
+    } else if (act_out == ACT_SOFTMAX) {
+        float m = live ? zv : -INFINITY;
+#pragma unroll
+        for (int sh = 1; sh < 16; sh <<= 1) m = fmaxf(m, __shfl_xor(m, sh, 16));
+        const float ex = live ? expf(zv - m) : 0.f;
+        float sm = ex;
+#pragma unroll
+        for (int sh = 1; sh < 16; sh <<= 1) sm += __shfl_xor(sm, sh, 16);
+        xo = ex * (1.0f / sm);
+    } else {
+        xo = act_fn(act_out, zv);
+    }
+    if (!live) return 0.f;
+    const float t1 = (o == label) ? 1.0f : 0.0f;
+    const float dd = (loss == LOSS_XENT) ? (xo - t1) : (xo - t1) * act_deriv(act_out, xo);
+    return to_f<TD>(from_f<TD>(dd));
+}
+
+// ------------------------------------------------------------------------------------
+// Output layer: z = W x + b over <= 16 outputs, the output activation (eq. (3), softmax eq. (5)),
+// then either the output error (training, eq. (9) or (10)) or the predicted class, cost and correct
+// count (inference).
 
 struct RowArgs {
     const void* x;  // input activations: xrows (data set) or workspace [z][rows][ld]
@@ -2131,75 +2163,26 @@ struct RowArgs {
     double* cost;      // inference: [rows] cost of each data-set row (nullable; needs y)
 };
 
-template <typename TX, typename TW, typename TD>
-__global__ __launch_bounds__(256) void out_layer_kernel(RowArgs a) {
-    const int lane = threadIdx.x & 63;
-    const int row = blockIdx.x * 4 + (threadIdx.x >> 6);
-    const int z = blockIdx.z;
-    int64_t v = shard_len(a.n_total, a.k_rep, z) - a.r0;
-    const int valid = (int)(v < 0 ? 0 : (v > a.step_rows ? a.step_rows : v));
-    if (row >= valid) return;
-    const int64_t drow = shard_start(a.n_total, a.k_rep, z) + a.r0 + row;  // data-set row
-    const TX* x = a.x_xrows ? (const TX*)a.x + (size_t)drow * a.x_ld
-                            : (const TX*)a.x + (size_t)z * a.x_z + (size_t)row * a.x_ld;
-    const TW* W = (const TW*)a.w + (size_t)z * a.w_z;
-    float acc[MAX_OUT];
-#pragma unroll
-    for (int o = 0; o < MAX_OUT; ++o) acc[o] = 0.f;
-    for (int i = lane; i < a.H; i += 64) {
-        float xi = to_f<TX>(x[i]);
-        if constexpr (sizeof(TW) == 2 && sizeof(TX) == 4) xi = bf2f(f2bf(xi));  // bf16 operand
-#pragma unroll
-        for (int o = 0; o < MAX_OUT; ++o)
-            if (o < a.O) acc[o] += to_f<TW>(W[(size_t)o * a.H + i]) * xi;
-    }
-    const float* b = a.bias + (size_t)z * a.bias_z;
-    float zo[MAX_OUT], xo[MAX_OUT];
-#pragma unroll
-    for (int o = 0; o < MAX_OUT; ++o) zo[o] = (o < a.O) ? wave_sum(acc[o]) + b[o] : 0.f;
-    if (a.act == ACT_SOFTMAX) {
-        float m = zo[0];
-#pragma unroll
-        for (int o = 1; o < MAX_OUT; ++o) if (o < a.O) m = fmaxf(m, zo[o]);
-        float s = 0.f;
-#pragma unroll
-        for (int o = 0; o < MAX_OUT; ++o) { xo[o] = (o < a.O) ? expf(zo[o] - m) : 0.f; s += xo[o]; }
-        const float inv = 1.0f / s;
-#pragma unroll
-        for (int o = 0; o < MAX_OUT; ++o) xo[o] *= inv;
-    } else {
-#pragma unroll
-        for (int o = 0; o < MAX_OUT; ++o) xo[o] = act_fn(a.act, zo[o]);
-    }
-    const int label = a.y[drow];
-    TD* d = (TD*)a.delta + (size_t)z * a.d_z + (size_t)row * a.O;
-    if (lane < a.O) {
-        float xv = 0.f;
-#pragma unroll
-        for (int o = 0; o < MAX_OUT; ++o) if (o == lane) xv = xo[o];
-        const float e = (lane == label) ? 1.0f : 0.0f;
-        const float dv = (a.loss == LOSS_XENT) ? (xv - e) : (xv - e) * act_deriv(a.act, xv);
-        d[lane] = from_f<TD>(dv);
-    }
-}
-
-// The output layer of an inference: 16 rows per workgroup, z = X W^T + b on v_mfma_f32_16x16x4_f32
+// 16 rows of one CN (of the data set in an inference) per workgroup, z = X W^T + b on v_mfma_f32_16x16x4_f32
 // with the outputs padded to 16 (the four waves split H in blocks of 16, loaded 16 or 8 bytes a lane
 // in the instruction's layout; their partial tiles are added in LDS in wave order), then one lane per
-// (row, output): activation, argmax, cost and count by reductions over the 16 lanes of a row.
+// (row, output): activation, then the output error, or argmax, cost and count by reductions over
+// the 16 lanes of a row.
 // Bound: the read of the hidden activations.  (One wavefront per row, each lane adding up to 16
 // outputs and reducing every one over the wave, took 79 us for 8,192 rows of 1,024, 0.4 TB/s.)
-template <typename TX, typename TW>
-__global__ __launch_bounds__(256) void infer_out_kernel(RowArgs a) {
+template <typename TX, typename TW, typename TD, bool TRAIN>
+__global__ __launch_bounds__(256) void out_layer_kernel(RowArgs a) {
     __shared__ float part[4][16][17];
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, l16 = lane & 15, g = lane >> 4;
-    const int row0 = blockIdx.x * 16;
-    const int64_t v = a.n_total - a.r0;
-    const int valid = (int)(v > a.step_rows ? a.step_rows : v);  // (the rows of this chunk)
+    const int row0 = blockIdx.x * 16, zi = blockIdx.z;
+    const int64_t v = shard_len(a.n_total, a.k_rep, zi) - a.r0;
+    const int valid = (int)(v < 0 ? 0 : v > a.step_rows ? a.step_rows : v);  // (the rows of this step or chunk)
+    if (row0 >= valid) return;
+    const int64_t d0 = shard_start(a.n_total, a.k_rep, zi) + a.r0;  // data-set row of row 0
     {
         const int r = min(row0 + l16, valid - 1);
-        const TX* x = (const TX*)a.x + (size_t)(a.x_xrows ? a.r0 + r : r) * a.x_ld;
-        const TW* W = (const TW*)a.w + (size_t)min(l16, a.O - 1) * a.H;
+        const TX* x = (const TX*)a.x + (a.x_xrows ? (size_t)(d0 + r) * a.x_ld : (size_t)zi * a.x_z + (size_t)r * a.x_ld);
+        const TW* W = (const TW*)a.w + (size_t)zi * a.w_z + (size_t)min(l16, a.O - 1) * a.H;
         constexpr int PF = 4;  // blocks in flight, each with a chain of sums of its own
         f4 acc[PF];
 #pragma unroll
@@ -2234,8 +2217,13 @@ __global__ __launch_bounds__(256) void infer_out_kernel(RowArgs a) {
     __syncthreads();
     const int rr = tid >> 4, o = tid & 15, row = row0 + rr;
     const bool live = row < valid && o < a.O;
-    const int64_t drow = a.r0 + row;
-    const float z = (part[0][rr][o] + part[1][rr][o]) + (part[2][rr][o] + part[3][rr][o]) + (o < a.O ? a.bias[o] : 0.f);
+    const int64_t drow = d0 + row;
+    const float z = (part[0][rr][o] + part[1][rr][o]) + (part[2][rr][o] + part[3][rr][o]) + (o < a.O ? a.bias[(size_t)zi * a.bias_z + o] : 0.f);
+    if constexpr (TRAIN) {
+        const float d = out_error<TD, true>(z, live, o, row < valid ? a.y[drow] : -1, a.act, a.loss);
+        if (live) ((TD*)a.delta)[(size_t)zi * a.d_z + (size_t)row * a.O + o] = from_f<TD>(d);
+        return;
+    }
     float xo;
     if (a.act == ACT_SOFTMAX) {
         const float m = row_allmax16(o < a.O ? z : -INFINITY);
@@ -2379,37 +2367,6 @@ __global__ __launch_bounds__(256) void upd_small_kernel(UpdSmallArgs a) {
 }
 
 // ------------------------------------------------------------------------------------
-// Output activation and output error of one (row, output) lane, the 16 lanes of a row taking
-// part together (softmax over them): eq. (3) / (5) and (9) / (10); zero on dead lanes (rows
-// past the step or outputs past O); rounded to the error type TD.
-
-// DPP: the row reductions by DPP instead of shuffles through LDS (another order of the sum; the
-// whole wave active).
-template <typename TD, bool DPP = false>
-__device__ inline float out_error(float zv, bool live, int o, int label, int act_out, int loss) {
-    float xo;
-    if (DPP && act_out == ACT_SOFTMAX) {
-        const float m = row_allmax16(live ? zv : -INFINITY);
-        const float ex = live ? expf(zv - m) : 0.f;
-        xo = ex * (1.0f / row_allsum16(ex));
-    } else if (act_out == ACT_SOFTMAX) {
-        float m = live ? zv : -INFINITY;
-#pragma unroll
-        for (int sh = 1; sh < 16; sh <<= 1) m = fmaxf(m, __shfl_xor(m, sh, 16));
-        const float ex = live ? expf(zv - m) : 0.f;
-        float sm = ex;
-#pragma unroll
-        for (int sh = 1; sh < 16; sh <<= 1) sm += __shfl_xor(sm, sh, 16);
-        xo = ex * (1.0f / sm);
-    } else {
-        xo = act_fn(act_out, zv);
-    }
-    if (!live) return 0.f;
-    const float t1 = (o == label) ? 1.0f : 0.0f;
-    const float dd = (loss == LOSS_XENT) ? (xo - t1) : (xo - t1) * act_deriv(act_out, xo);
-    return to_f<TD>(from_f<TD>(dd));
-}
-
 // The last layer's outputs and errors when its products are fused into the hidden layer's
 // split-bf16 kernels: z2 = sum of the forward tiles' partial sums (tile order) + b2, then the
 // output error of each row, one lane per (row, output), into dout [z][rows][16] (zeros past O
@@ -2444,6 +2401,124 @@ __global__ __launch_bounds__(256) void out_err_kernel(OutErrArgs a) {
     }
     const int label = row < valid ? a.y[shard_start(a.n_total, a.k_rep, z) + a.r0 + row] : -1;
     a.dout[((size_t)z * a.step_rows + row) * 16 + o] = out_error<float>(zv, live, o, label, a.act_out, a.loss);
+}
+
+// ------------------------------------------------------------------------------------
+// The hidden error behind a narrow last layer (O <= 16) and that layer's update, by columns of the
+// hidden layer: each wave owns 16 hidden neurons of one CN over the whole batch.  Per 16 rows, with
+// the rows' activations in the matrix instruction's accumulator layout (loaded once, two tiles
+// ahead):
+//   S = delta W (eq. (11), the pre-update W, 4 instructions over the 16 outputs) and d = S * phi'(x)
+//   stored; dW += delta^T x (4 instructions: the activations as held are the second operand, the
+//   rows of an instruction being 4 g + r).
+// At the end W -= lr / B_t dW (master; the bf16 shadow refreshed) and, in the first workgroup of a
+// CN, b -= lr / B_t sum_r delta.  Bound: latency and the pass over the activations.  784-200-104-10,
+// K = 6, B = 100 (a width that is no multiple of 16, where tail_kernel does not apply): 95 us a step
+// in one thread per weight or row and a wavefront per row -> 19 us with out_layer_kernel.
+struct LastArgs {
+    const void* delta;  // output errors [z][rows][O] (TH)
+    int64_t dn_z;
+    const void* x;      // last hidden activations [z][rows][H] (TH)
+    void* d;            // hidden errors, same layout
+    int64_t x_z;
+    const void* wop;    // W_L operand [O][H] (+ z * w_z): fp32 master or bf16 shadow
+    float* w;           // W_L fp32 master (+ z * w_z)
+    bf16_t* shadow;     // bf16 shadow of W_L (+ z * w_z), nullable
+    float* bias;        // b_L [O] (+ z * w_z)
+    int64_t w_z;
+    int H, O, act_hid;
+    float lr;
+    int64_t n_total;
+    int k_rep;
+    int64_t r0;
+    int step_rows;
+};
+constexpr int LAST_ROWS = 128;  // rows of output errors staged at a time
+
+template <typename TH>
+__global__ __launch_bounds__(256) void last_layer_kernel(LastArgs a) {
+    __shared__ float dl[LAST_ROWS][17];
+    __shared__ float bsum[16][17];
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, l16 = lane & 15, g = lane >> 4;
+    const int z = blockIdx.z, H = a.H, O = a.O;
+    const int64_t v = shard_len(a.n_total, a.k_rep, z) - a.r0;
+    const int valid = (int)(v < 0 ? 0 : v > a.step_rows ? a.step_rows : v);
+    if (valid == 0) return;
+    const int col = (blockIdx.x * 4 + wave) * 16 + l16;  // this lane's hidden neuron
+    const bool cok = col < H;
+    const int cc = cok ? col : 0;
+    const TH* wop = (const TH*)a.wop + (size_t)z * a.w_z;
+    float wq[4];
+#pragma unroll
+    for (int q = 0; q < 4; ++q) wq[q] = cok && 4 * q + g < O ? to_f<TH>(wop[(size_t)min(4 * q + g, O - 1) * H + cc]) : 0.f;
+    const TH* x = (const TH*)a.x + (size_t)z * a.x_z;
+    TH* d = (TH*)a.d + (size_t)z * a.x_z;
+    const TH* dn = (const TH*)a.delta + (size_t)z * a.dn_z;
+    f4 dw = {0.f, 0.f, 0.f, 0.f};
+    float sb = 0.f;  // sum of output tid % 16 over the rows tid / 16, + 16, ...
+    const int ntile = (valid + 15) >> 4;
+    TH xb[2][4];  // the next two tiles' activations
+    auto load = [&](int t, TH (&to)[4]) {
+#pragma unroll
+        for (int r = 0; r < 4; ++r) to[r] = x[(size_t)min(16 * t + 4 * g + r, valid - 1) * H + cc];
+    };
+    // row tile tt of the staged rows, tile t of the step
+    auto tile = [&](int tt, int t, TH (&xt)[4]) {
+        float xv[4];
+#pragma unroll
+        for (int r = 0; r < 4; ++r) xv[r] = to_f<TH>(xt[r]);
+        load(t + 2, xt);  // (past the step: its last row, unused)
+        f4 s = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+        for (int q = 0; q < 4; ++q) s = __builtin_amdgcn_mfma_f32_16x16x4f32(dl[16 * tt + l16][4 * q + g], wq[q], s, 0, 0, 0);
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+            // (rows past the step have zero errors, so their activations do not count in dW)
+            dw = __builtin_amdgcn_mfma_f32_16x16x4f32(dl[16 * tt + 4 * g + r][l16], xv[r], dw, 0, 0, 0);
+            const int row = 16 * t + 4 * g + r;
+            if (row < valid && cok) d[(size_t)row * H + col] = from_f<TH>(s[r] * act_deriv(a.act_hid, xv[r]));
+        }
+    };
+    load(0, xb[0]);
+    load(1, xb[1]);
+    for (int c0 = 0; c0 < valid; c0 += LAST_ROWS) {
+        __syncthreads();
+        for (int e = tid; e < LAST_ROWS * 16; e += 256) {
+            const int r = e >> 4, o = e & 15;
+            const float dv = c0 + r < valid && o < O ? to_f<TH>(dn[(size_t)(c0 + r) * O + o]) : 0.f;
+            dl[r][o] = dv;
+            sb += dv;
+        }
+        __syncthreads();
+        for (int tt = 0; tt < LAST_ROWS / 16; tt += 2) {
+            const int t = c0 / 16 + tt;
+            if (t >= ntile) break;
+            tile(tt, t, xb[0]);
+            if (t + 1 < ntile) tile(tt + 1, t + 1, xb[1]);
+        }
+    }
+    const float scale = a.lr / (float)valid;
+    float* wm = a.w + (size_t)z * a.w_z;
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+        const int o = 4 * g + r;
+        if (o < O && cok) {
+            const size_t i = (size_t)o * H + col;
+            const float w = wm[i] - scale * dw[r];
+            wm[i] = w;
+            if (a.shadow) a.shadow[(size_t)z * a.w_z + i] = f2bf(w);
+        }
+    }
+    if (blockIdx.x == 0) {
+        bsum[tid >> 4][tid & 15] = sb;
+        __syncthreads();
+        if (tid < O) {
+            float sum = 0.f;
+#pragma unroll
+            for (int p = 0; p < 16; ++p) sum += bsum[p][tid];
+            a.bias[(size_t)z * a.w_z + tid] -= scale * sum;
+        }
+    }
 }
 
 // ------------------------------------------------------------------------------------

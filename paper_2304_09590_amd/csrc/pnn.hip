@@ -510,7 +510,13 @@ pnn_status minibatch_step(pnn_net* n, const float* X, const int32_t* Y, int64_t 
     const int Hl = L >= 2 ? n->sizes[L - 1] : 0;
     const int trg = tail_rows(Hl, B);
     const size_t tail_smem = trg > 0 ? (size_t)tail_lds_floats(Hl, trg) * sizeof(float) : 0;
-    const bool fuse_tail = !fx3 && L >= 2 && n->sizes[L] <= MAX_OUT && trg > 0 && tail_smem <= 160 * 1024;
+    // (One workgroup per CN: its time grows with the batch times the layer, however few CNs there
+    // are.  out_layer_kernel and last_layer_kernel spread that over the chip in two launches: from
+    // 128 x 256 on, while the CNs alone do not fill the CUs -- us a step, one kernel / two: 128 x 256,
+    // K = 1 38 / 34, K = 64 112 / 107, K = 256 243 / 248; 64 x 256, K = 64 71 / 71, bf16 62 / 64;
+    // 64 x 1024, K = 16 105 / 79; 300 x 32 51 / 52; 300 x 1024, K = 64 689 / 544.)
+    const bool spread = (int64_t)B * Hl >= 32768 && K <= 128;
+    const bool fuse_tail = !fx3 && L >= 2 && n->sizes[L] <= MAX_OUT && trg > 0 && tail_smem <= 160 * 1024 && !spread;
     if (fuse_tail) {
         TailArgs a;
         memset(&a, 0, sizeof a);
@@ -544,15 +550,32 @@ pnn_status minibatch_step(pnn_net* n, const float* X, const int32_t* Y, int64_t 
         a.n_total = N; a.k_rep = K; a.r0 = r0; a.step_rows = B;
         a.y = Y;
         a.delta = n->del_ws[L]; a.d_z = (int64_t)B * n->sizes[L];
-        dim3 grid((B + 3) / 4, 1, K);
+        dim3 grid((B + 15) / 16, 1, K);
         Launch lc(n, s, "out_layer");
-        if (L == 1) out_layer_kernel<float, TH, TH><<<grid, 256, 0, s>>>(a);
-        else out_layer_kernel<TH, TH, TH><<<grid, 256, 0, s>>>(a);
+        if (L == 1) out_layer_kernel<float, TH, TH, true><<<grid, 256, 0, s>>>(a);
+        else out_layer_kernel<TH, TH, TH, true><<<grid, 256, 0, s>>>(a);
+        TRY(lc.done());
+    }
+    // the hidden error behind a narrow last layer, and that layer's update
+    const bool last = !fuse_tail && !fx3 && L >= 2 && n->sizes[L] <= MAX_OUT;
+    if (last) {
+        LastArgs a;
+        memset(&a, 0, sizeof a);
+        a.delta = n->del_ws[L]; a.dn_z = (int64_t)B * n->sizes[L];
+        a.x = n->act_ws[L - 1]; a.d = n->del_ws[L - 1]; a.x_z = (int64_t)B * Hl;
+        a.wop = (const char*)Wop + n->off_w[L - 1] * (BF ? 2 : 4);
+        a.w = n->theta + n->off_w[L - 1];
+        a.shadow = BF ? n->shadow + n->off_w[L - 1] : nullptr;
+        a.bias = n->theta + n->off_b[L - 1]; a.w_z = ps;
+        a.H = Hl; a.O = n->sizes[L]; a.act_hid = n->act[L - 2]; a.lr = n->cfg.lr;
+        a.n_total = N; a.k_rep = K; a.r0 = r0; a.step_rows = B;
+        Launch lc(n, s, "last_layer");
+        last_layer_kernel<TH><<<dim3((Hl + 63) / 64, 1, K), 256, 0, s>>>(a);
         TRY(lc.done());
     }
     // hidden errors, back to front, with the pre-update weights (eq. (11))
     for (int l = L - 1; l >= 1; --l) {
-        if ((fuse_tail || fx3) && l == L - 1) continue;  // (in the fused last layer)
+        if ((fuse_tail || fx3 || last) && l == L - 1) continue;  // (with the last layer)
         const int Hl = n->sizes[l], On = n->sizes[l + 1];
         if (On <= MAX_OUT) {
             BwdSmallArgs a;
@@ -578,7 +601,7 @@ pnn_status minibatch_step(pnn_net* n, const float* X, const int32_t* Y, int64_t 
     }
     // updates, eq. (12)-(13) averaged over the batch
     // (bf16, two wide layers before a fused last layer: both weight updates in one launch)
-    const bool upd2 = BF && L == 3 && fuse_tail && n->sizes[1] > MAX_OUT && n->sizes[2] > MAX_OUT && B <= 64 &&
+    const bool upd2 = BF && L == 3 && (fuse_tail || last) && n->sizes[1] > MAX_OUT && n->sizes[2] > MAX_OUT && B <= 64 &&
                       K % 8 == 0 && n->sizes[0] % 4 == 0 && n->sizes[1] % 4 == 0 && n->sizes[2] % 4 == 0;
     if constexpr (BF) if (upd2) {
         GemmArgs gg[2];
@@ -604,7 +627,7 @@ pnn_status minibatch_step(pnn_net* n, const float* X, const int32_t* Y, int64_t 
         TRY(lu.done());
     }
     for (int l = 1; l <= L; ++l) {
-        if ((fuse_tail || fx3) && l == L) continue;  // (in the fused last layer)
+        if ((fuse_tail || fx3 || last) && l == L) continue;  // (above)
         if (upd2 && l <= 2) continue;                // (above)
         const int In = n->sizes[l - 1], Out = n->sizes[l];
         if (Out <= MAX_OUT) {
@@ -1452,11 +1475,11 @@ static pnn_status run_inference(pnn_net* n, int32_t which, const float* x_dev, i
         Launch lc(n, s, "infer_out");
         if (n->bf16) {
             a.w = sh + n->off_w[L - 1];
-            if (L == 1) infer_out_kernel<float, bf16_t><<<grid, 256, 0, s>>>(a);
-            else infer_out_kernel<bf16_t, bf16_t><<<grid, 256, 0, s>>>(a);
+            if (L == 1) out_layer_kernel<float, bf16_t, float, false><<<grid, 256, 0, s>>>(a);
+            else out_layer_kernel<bf16_t, bf16_t, float, false><<<grid, 256, 0, s>>>(a);
         } else {
             a.w = th + n->off_w[L - 1];
-            infer_out_kernel<float, float><<<grid, 256, 0, s>>>(a);
+            out_layer_kernel<float, float, float, false><<<grid, 256, 0, s>>>(a);
         }
         TRY(lc.done());
     }

@@ -244,3 +244,21 @@ def test_inference_of_not_a_number():
     assert np.all(np.isnan(got[7])) and p[7] == 0
     assert np.array_equal(got[rest], clean[rest]) and np.array_equal(p[rest], ref[rest])
     net.close()
+
+
+# ------------------------------------------------------------------------------------
+# the last layer in two kernels (errors by row, then hidden errors and update by columns): widths that
+# are no multiple of 16 or 64, one and 16 outputs, batches of one staged block, one row more and
+# several, CNs whose last step has no rows
+
+@pytest.mark.parametrize("precision", [I.FP32, I.BF16_MIXED])
+@pytest.mark.parametrize("over,N", [
+    (dict(sizes=(784, 104, 10), batch=100, replicas=3), 3 * 130 + 1),
+    (dict(sizes=(784, 8, 1), acts=(I.SIGMOID, I.SIGMOID), batch=128, replicas=2), 2 * 140),
+    (dict(sizes=(784, 1024, 16), acts=(I.TANH, I.SOFTMAX), loss=I.LOSS_XENT, batch=129, replicas=2), 2 * 129 + 1),
+    (dict(sizes=(784, 272, 10), batch=300, replicas=2), 2 * 301 + 1),
+    (dict(sizes=(784, 64, 512, 10), acts=(I.TANH, I.SIGMOID, I.SIGMOID), batch=72, replicas=8), 8 * 80 + 3),
+])
+def test_last_layer_in_two_kernels(over, N, precision, monkeypatch):
+    monkeypatch.setenv("PNN_MB_PLAN", "launch")
+    train_both(I.WORKLOADS[2].scaled(precision=precision, **over), N, 2).close()
