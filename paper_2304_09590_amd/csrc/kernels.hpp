@@ -4275,6 +4275,9 @@ __global__ __launch_bounds__(MBP_THREADS) void mbp_kernel(MbpArgs a) {
                 for (int r = 0; r < RT; ++r)
                     *(f4*)(red + (((size_t)(wave * MT + mt) * RT + r) * 64 + lane) * 4) = acc[mt][r];
         }
+        // (also in a wave whose input blocks lie past the inputs, which has waited for no row: its
+        // cleared share words have to be out before any wave of the tile publishes this step)
+        wait_vm_all();
         lds_barrier();
 #pragma unroll
         for (int e0 = 0; e0 < MT * RT * 256; e0 += MBP_THREADS) {
@@ -4399,9 +4402,9 @@ __global__ __launch_bounds__(MBP_THREADS) void mbp_kernel(MbpArgs a) {
             dls[t * 17 + o] = out_error<TH, true>(z, live, o, yc[u], a.act2, a.loss);
         }
         // Every tile of the CN has published step c, so it has read every share of step c - 1 and
-        // before: this tile's share of step c - 2 is cleared, for step c + 2.  (The next step
-        // starts by waiting for all of the wave's accesses, so the words are cleared before the
-        // tile publishes step c + 1, which every reader of step c + 2 has waited for.)
+        // before: this tile's share of step c - 2 is cleared, for step c + 2.  (Before the next
+        // step's first barrier each wave waits for all of its accesses, so the words are cleared
+        // before the tile publishes step c + 1, which every reader of step c + 2 has waited for.)
         {
             unsigned long long* zc = (unsigned long long*)(a.zpart + ((size_t)(((c + 2) & 3) * K + k) * nrb + rb) * ZS);
             if (2 * tid < TB * O) __hip_atomic_store(zc + tid, ~0ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
