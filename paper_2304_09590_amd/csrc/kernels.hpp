@@ -4212,7 +4212,9 @@ __global__ __launch_bounds__(MBP_THREADS) void mbp_kernel(MbpArgs a) {
         // offset would be added behind the check -- and is formed here each time, opaque to the
         // compiler, which would keep one for every load in registers.)
         unsigned past = wave + MBP_WAVES * j < nib ? 0u : 0x70000000u;
+#ifdef __OPTIMIZE__  // (unoptimised code has it in a vector register)
         asm volatile("" : "+s"(past));
+#endif
 #pragma unroll
         for (int mt = 0; mt < MT; ++mt) {
             const unsigned vo = ((unsigned)((mt * 16 + l16) * In + wave * 16 + 4 * g) * 4u) | past;
