@@ -205,8 +205,8 @@ int32_t pnn_profile_read(pnn_net* net, const char** names, double* total_ms, int
  *  "per-sample persistent"  B = 1, one hidden layer of <= 128 neurons, sizes[0] <= 832: one
  *                           launch per epoch for each group of CNs whose workgroups fit the
  *                           device at once (all K CNs in one group where they fit);
- *  "per-sample chunked"     B = 1 otherwise; with one hidden layer of <= 384 neurons and
- *                           sizes[0] <= 832 the chunks of an epoch run in persistent launches as
+ *  "per-sample chunked"     B = 1 otherwise; with one hidden layer of <= 384 neurons,
+ *                           sizes[0] <= 832 and K <= 256 the chunks of an epoch run in persistent launches as
  *                           above (an epoch that is recorded into a graph: in launches per chunk);
  *  "mini-batch persistent"  fp32, one hidden layer, 2 <= B <= 32, <= 16 outputs,
  *                           sizes[0] % 16 == 0 and <= 832, H <= 512: one launch per epoch for

@@ -1133,14 +1133,20 @@ pnn_status pnn_init(const pnn_config* cfg, const float* theta0_host, void* hip_s
         // workgroups fit the CUs, one launch each.  Of the two, the one with the least estimated
         // time: launches x the relative time of a step (1 with 16-row tiles, 1.8 with 32-row
         // tiles, whose tiles do twice the work per chunk; 1.5 to 1.9 measured with 784-128-10
-        // nets, growing with the CNs in flight)
+        // nets, growing with the CNs in flight).  Above 128 neurons a chunk has half the steps and a
+        // step takes the live wave longer, so the tiles' work hides behind it: 1.2 up to 256
+        // neurons, 1.1 above (us a step, 16-row / 32-row tiles / launches per chunk: 784-256-10,
+        // K = 20 2.06 / 1.27 / 11.0, K = 64 4.97 / 3.38 / 11.2, K = 256 18.4 / 12.0 / 14.9;
+        // 784-384-10, K = 64 8.45 / 5.22 / 13.6, K = 256 31.5 / 18.4 / 21.3; where both take one
+        // launch 1.14 / 1.14 and 1.42 / 1.40).
+        const double rel = H <= 128 ? 1.8 : H <= 256 ? 1.2 : 1.1;
         int rt = 1, kg = 0;
         double best = 1e30;
         for (int r = 1; r <= 2; ++r) {
             const int nb = (H + 16 * r - 1) / (16 * r);
             const int g = std::min(K, cus / (1 + nb));
             if (g < 1) continue;
-            const double cost = (double)((K + g - 1) / g) * (r == 1 ? 1.0 : 1.8);
+            const double cost = (double)((K + g - 1) / g) * (r == 1 ? 1.0 : rel);
             if (cost < best) { best = cost; rt = r; kg = g; }
         }
         const int nrb = (H + 16 * rt - 1) / (16 * rt);
@@ -1154,7 +1160,10 @@ pnn_status pnn_init(const pnn_config* cfg, const float* theta0_host, void* hip_s
         n->pspecial = n->act[0] == PNN_SIGMOID && n->act[1] == PNN_SIGMOID && cfg->loss == PNN_LOSS_MSE && O == 10;
         const void* fn = persistent_fn(n);
         int per_cu = 0;
-        bool fits = H <= PSGD_MAX_H && In <= 4 * MAX_IB * 16 && kg >= 1;
+        // (above 128 neurons up to 256 CNs, where it is the faster one in all widths; the launches per
+        // chunk take all CNs at once -- us a step, this kernel / those: 784-136-10, K = 256
+        // 8.4 / 11.6, K = 512 19.6 / 16.2; 784-384-10, K = 512 43.3 / 43.2, K = 1,024 118 / 91)
+        bool fits = H <= PSGD_MAX_H && (H <= 128 || K <= 256) && In <= 4 * MAX_IB * 16 && kg >= 1;
         if (fits && hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)n->psmem) != hipSuccess)
             fits = false;
         if (fits && hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, fn, 256, n->psmem) != hipSuccess) fits = false;

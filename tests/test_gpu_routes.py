@@ -54,6 +54,9 @@ def train_both(w, N, epochs):
     (dict(sizes=(784, 384, 1), replicas=2), 2 * 31),
     (dict(sizes=(784, 256, 10), replicas=20), 20 * 40 + 3),   # 32-row tiles
     (dict(sizes=(784, 144, 10), replicas=70), 70 * 34 + 1),   # two launches of 35 CNs
+    (dict(sizes=(784, 264, 10), replicas=16), 16 * 40 + 3),   # 32-row tiles, six neurons per lane
+    (dict(sizes=(784, 136, 10), replicas=256), 256 * 3 + 1),  # the most CNs of the persistent launches
+    (dict(sizes=(784, 136, 10), replicas=257), 257 * 3 + 1),  # launches per chunk
 ])
 def test_wide_per_sample(over, N):
     train_both(I.WORKLOADS[1].scaled(**over), N, 2).close()
