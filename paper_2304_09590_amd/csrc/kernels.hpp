@@ -115,6 +115,23 @@ __device__ inline float act_fast(int a, float z) {
     }
 }
 
+// The sigmoid of the per-sample steps above 128 neurons, as accurate as act_fn's at two thirds of its
+// instructions: e = exp2(h) of h = x log2 e on the hardware; the remainder of that product,
+// r = x - h ln 2 (ln 2 in two parts), corrects it to e + e r, unrounded; the reciprocal y of d = 1 + e
+// takes one Newton step towards 1 / (d + e r).  Largest relative error against 64 bits in [-15, 15]:
+// act_fn 1.24e-7, this one 1.22e-7, act_fast 9.4e-7.  Beyond |z| = 87, where e leaves the normal
+// range (or z is no number), the hardware's values stand: within 1.2e-38.
+template <bool FAST>
+__device__ inline float act_step(int a, float z) {
+    if (FAST || a != ACT_SIGMOID) return act_fast(a, z);
+    const float h = -1.44269504f * z;
+    const float e = __builtin_amdgcn_exp2f(h);
+    const float r = __builtin_fmaf(h, 1.90465430e-9f, __builtin_fmaf(h, -0.693147182f, -z));
+    const float d = 1.0f + e, y = __builtin_amdgcn_rcpf(d);
+    const float q = __builtin_fmaf(-(e * r), y, __builtin_fmaf(-d, y, 1.0f));
+    return __builtin_fabsf(z) < 87.0f ? __builtin_fmaf(q, y, y) : y;
+}
+
 // maximum / sum over the 16 lanes of a row, by DPP (defined with the other cross-lane helpers)
 __device__ inline float row_allmax16(float v);
 __device__ inline float row_allsum16(float v);
@@ -3465,8 +3482,9 @@ __device__ inline void lds_publish(int* f, int v) {
 // and the fold waves' accumulators grow as HW T, and so does the matrix work of a fold, so twice
 // the neurons with half the steps cost the same of each; a chunk of 32 steps still takes the live
 // wave far longer (24 us) than the tiles need for their next Q.  Bound: the live wave's chain of
-// dependent steps, 0.52 us a step for 128 neurons, 0.74 us for 256 and 1.0 us for 384.  784-256-10,
-// K = 4, 8,000 rows: 20.2 ms in psgd_chunk_kernel launches (9.9 us a step) -> 1.5 ms.
+// dependent steps, 0.52 us a step for 128 neurons, 0.85 us for 256 (0.74 with act_fast, which is
+// less exact than the launches per chunk are).  784-256-10, K = 4, 8,000 rows: 21.5 ms in
+// psgd_chunk_kernel launches (9.9 us a step) -> 1.92 ms.
 // Counters (LDS): d1done (steps whose d1 is in hist), cdone (rows whose cpre is ready),
 // rdy (per folding wave: leading blocks whose rows of Pl are final), gready (chunks whose
 // Gram blocks and labels are in LDS), pubd (blocks whose d1 has been copied out of hist),
@@ -3481,6 +3499,7 @@ __device__ __attribute__((always_inline)) inline void psgd_rec(const PsgdPArgs& 
     constexpr int NLIVE = 5;        // latest errors whose terms the live wave adds itself (<= BS; the
                                     // live step below is written out for five)
     constexpr int NB = T / BS;      // blocks per chunk
+    constexpr bool FAST = T == 64;  // the activations' form (act_step)
     static_assert(T == 64 || T == 32, "chunks of 64 or 32 steps");
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int H = a.H, K = a.k_rep;
@@ -3612,7 +3631,7 @@ __device__ __attribute__((always_inline)) inline void psgd_rec(const PsgdPArgs& 
 #pragma unroll
             for (int j = 0; j < NH; ++j) {
                 const float z1 = pln[j] + b1[j] - lr * corr[j];
-                a1[j] = (lane + 64 * j < H) ? act_fast(act1, z1) : 0.f;
+                a1[j] = (lane + 64 * j < H) ? act_step<FAST>(act1, z1) : 0.f;
                 na[j] = -lr * a1[j];
             }
             float z2;
@@ -3643,10 +3662,11 @@ __device__ __attribute__((always_inline)) inline void psgd_rec(const PsgdPArgs& 
             float x2;
             if (act2 == ACT_SOFTMAX) {
                 const float m = row_allmax16(owner ? z2 : -INFINITY);
-                const float e = owner ? __expf(z2 - m) : 0.f;
-                x2 = e * __builtin_amdgcn_rcpf(row_allsum16(e));
+                const float e = !owner ? 0.f : FAST ? __expf(z2 - m) : expf(z2 - m);
+                const float es = row_allsum16(e);
+                x2 = e * (FAST ? __builtin_amdgcn_rcpf(es) : 1.0f / es);
             } else {
-                x2 = act_fast(act2, z2);
+                x2 = act_step<FAST>(act2, z2);
             }
             const float e = (own == label) ? 1.0f : 0.0f;
             const float dv = (loss == LOSS_XENT) ? (x2 - e) : (x2 - e) * act_deriv(act2, x2);

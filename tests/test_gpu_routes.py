@@ -62,6 +62,55 @@ def test_wide_per_sample(over, N):
     train_both(I.WORKLOADS[1].scaled(**over), N, 2).close()
 
 
+def first_step_w2(H, act2, b1, b2):
+    """W2 after an epoch from W2 = 0 with eta = 1 and the cross-entropy error, in which only the first
+    row counts: -(x2 - e) a1^T of the activations of the biases themselves.  The first row is zero; the
+    others are one at input 0, whose weights of -1000 leave their hidden activations zero."""
+    w = I.WORKLOADS[1].scaled(sizes=(784, H, len(b2)), acts=(I.SIGMOID, act2), loss=I.LOSS_XENT, lr=1.0, replicas=1)
+    W1 = np.zeros((H, 784))
+    W1[:, 0] = -1000
+    net = make_net(w, np.concatenate([W1.ravel(), b1, np.zeros(H * len(b2)), b2]).astype(np.float32))
+    X = np.zeros((200, 784), np.float32)
+    X[1:, 0] = 1
+    net.train_epoch(dev(X), dev(np.zeros(200, np.int32)))
+    W2 = net.get_params(0)[785 * H:-len(b2)].astype(np.float64).reshape(len(b2), H)
+    net.close()
+    return W2
+
+
+@pytest.mark.parametrize("H", [136, 256, 264, 384])
+def test_wide_per_sample_activations_are_exact(H):
+    """The activations are as exact as the launches per chunk make them (e^x within one ulp, 1 + e and
+    the quotient within half an ulp each: 2.4e-7 in all; the hardware's exp2 and reciprocal alone
+    are off by 9e-7 at z = -15)."""
+    def sig(z):
+        return 1 / (1 + np.exp(-z.astype(np.float64)))
+    b1 = np.linspace(-15, 4, H).astype(np.float32)
+    # hidden: the output of b2 = 0 is 0.5 exactly, and so is its error (the label is output 0)
+    W2 = first_step_w2(H, I.SIGMOID, b1, np.zeros(2, np.float32))
+    assert np.max(np.abs(W2[1] / -0.5 / sig(b1) - 1)) <= 2.4e-7
+    # output: a1 = 0.5 exactly
+    b2 = -3 * np.arange(10).astype(np.float32)
+    W2 = first_step_w2(H, I.SIGMOID, np.zeros(H, np.float32), b2)
+    assert np.max(np.abs(W2[1:, 0] / -0.5 / sig(b2)[1:] - 1)) <= 2.4e-7
+    # softmax: e^x within one ulp, a sum of ten within one ulp and four roundings, 1 / sum and the
+    # product within half an ulp each
+    W2 = first_step_w2(H, I.SOFTMAX, np.zeros(H, np.float32), b2)
+    e = np.exp(b2.astype(np.float64))
+    assert np.max(np.abs(W2[1:, 0] / -0.5 / (e / e.sum())[1:] - 1)) <= 6e-7
+
+
+def test_wide_per_sample_activations_at_the_ends_of_the_range():
+    """Sigmoids of -inf, -100 and 100 are 0, 0 and 1 (the hardware's e^x and reciprocal stand there,
+    within the smallest normal number), and that of NaN is NaN."""
+    b1 = np.zeros(256, np.float32)
+    b1[:3] = -np.inf, -100, 100
+    W2 = first_step_w2(256, I.SIGMOID, b1, np.zeros(2, np.float32))
+    assert np.allclose(W2[1, :4], [0, 0, -0.5, -0.25], rtol=0, atol=1.2e-38)
+    b1[3] = np.nan
+    assert np.isnan(first_step_w2(256, I.SIGMOID, b1, np.zeros(2, np.float32))).all()
+
+
 def test_wide_per_sample_late_tiles(monkeypatch):
     """Half of the tile workgroups start late: the sequential workgroup waits for every tile."""
     monkeypatch.setenv("PNN_TEST_TILE_DELAY", "2000")
