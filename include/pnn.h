@@ -207,7 +207,8 @@ int32_t pnn_profile_read(pnn_net* net, const char** names, double* total_ms, int
  *                           device at once (all K CNs in one group where they fit);
  *  "per-sample chunked"     B = 1 otherwise; with one hidden layer of <= 384 neurons,
  *                           sizes[0] <= 832 and K <= 256 the chunks of an epoch run in persistent launches as
- *                           above (an epoch that is recorded into a graph: in launches per chunk);
+ *                           above where that is faster (few CNs or long slices; an epoch that is
+ *                           recorded into a graph: in launches per chunk);
  *  "mini-batch persistent"  fp32, one hidden layer, 2 <= B <= 32, <= 16 outputs,
  *                           sizes[0] % 16 == 0 and <= 832, H <= 512: one launch per epoch for
  *                           each group of CNs whose ceil(H / 16) (or ceil(H / 32)) tile

@@ -109,6 +109,7 @@ struct pnn_net {
     int nrb = 0;             // tile workgroups per CN
     int kgroup = 0;          // CNs per launch of a persistent plan (all K, or groups that fit the CUs)
     int prt = 1;             // 16-row sub-tiles per tile workgroup
+    int64_t ps_min_rows = 0; // rows of the longest slice from which the persistent kernel is taken (above 128 neurons)
     int* flags = nullptr;    // per-sample plan: qready[2][K] (by chunk parity), dready[K], abort
     float* qbuf = nullptr;   // [2][K][T][H]
     float* gramx = nullptr;  // [K][nch-1][T][T]
@@ -706,6 +707,26 @@ const void* persistent_fn(const pnn_net* n) { return n->prt == 2 ? persistent_fn
 constexpr int PSGD_MAX_H = 384;
 int live_width(int H) { return H <= 64 ? 64 : H <= 128 ? 128 : H <= 256 ? 256 : PSGD_MAX_H; }
 
+// Per-sample SGD above 128 neurons: rows of the longest slice from which an epoch in `groups`
+// persistent launches is faster than the launches per chunk, which take all CNs at once; 0 if never.
+// Estimates in us, fitted to 1,064 epochs (both sides measured; the one taken is at most 3 %
+// slower than the other in all but 22, and 12 % at most): a persistent launch costs a start-up (its
+// tiles read W1, the first input sums) and a step of its live wave, three times longer in the
+// general kernel than in the one for sigmoids, quadratic cost and ten outputs; the launches per chunk
+// a longer step, whose memory traffic grows with the CNs.  A pass, persistent / per chunk, 784-256-10:
+// sigmoids, 256 rows a CN, K = 4 0.35 / 2.7 ms, K = 128 1.70 / 3.04, and with 32 rows 0.60 / 0.43;
+// tanh and softmax, 256 rows, K = 64 2.27 / 2.47, K = 128 3.86 / 2.66.
+int64_t psgd_min_rows(int H, int In, int K, int groups, bool special, bool softmax) {
+    const double in = In / 784.0, kh = (double)K * H * in;
+    const double start_p = groups * (52.0 + 57.0 * in);
+    const double step_p = groups * (special ? (H <= 256 ? 0.90 : 1.22) : (H <= 256 ? 2.55 : 3.40));
+    const double start_c = 20.0 + 39.0 * in + 1.2e-3 * kh;
+    const double step_c = 5.1 + 0.0105 * H + (H > 256 ? 0.6 : 0.0) + 1.4 * in + (softmax ? 0.0 : 1.0) + 7e-5 * kh;
+    if (step_p >= step_c) return 0;
+    const double rows = std::ceil(std::max(start_p - start_c, 0.0) / (step_c - step_p));
+    return rows > 1e6 ? 0 : std::max<int64_t>(1, (int64_t)rows);
+}
+
 // floats of the Gram blocks of an epoch with slices of nmax rows, in the launches per chunk
 size_t psgd_gram_elems(int K, int64_t nmax, int T) { return (size_t)K * ((nmax + T - 1) / T) * T * T; }
 
@@ -872,12 +893,12 @@ bool capturing(hipStream_t s) {
 }
 
 pnn_status psgd_epoch(pnn_net* n, const float* X, const int32_t* Y, int64_t N, hipStream_t s) {
-    // (above 128 neurons an epoch recorded into a graph takes the launches per chunk, whose
-    // workspaces those nets keep: a persistent launch is cooperative and its time-out is read
-    // from the host afterwards)
-    if (n->persistent && !(n->T > 0 && capturing(s))) return psgd_persistent_epoch(n, X, Y, N, s);
+    // (above 128 neurons an epoch of short slices, and one recorded into a graph, takes the launches
+    // per chunk, whose workspaces those nets keep: a persistent launch is cooperative and its
+    // time-out is read from the host afterwards)
     const int K = n->cfg.replicas, T = n->T, H = n->sizes[1], In = n->sizes[0];
     const int64_t nmax = shard_len(N, K, 0);
+    if (n->persistent && !(T > 0 && (nmax < n->ps_min_rows || capturing(s)))) return psgd_persistent_epoch(n, X, Y, N, s);
     const int nch = (int)((nmax + T - 1) / T);
     const size_t need = psgd_gram_elems(K, nmax, T);
     if (need > n->gram_elems) {
@@ -1160,10 +1181,14 @@ pnn_status pnn_init(const pnn_config* cfg, const float* theta0_host, void* hip_s
         n->pspecial = n->act[0] == PNN_SIGMOID && n->act[1] == PNN_SIGMOID && cfg->loss == PNN_LOSS_MSE && O == 10;
         const void* fn = persistent_fn(n);
         int per_cu = 0;
-        // (above 128 neurons up to 256 CNs, where it is the faster one in all widths; the launches per
-        // chunk take all CNs at once -- us a step, this kernel / those: 784-136-10, K = 256
-        // 8.4 / 11.6, K = 512 19.6 / 16.2; 784-384-10, K = 512 43.3 / 43.2, K = 1,024 118 / 91)
+        // (above 128 neurons up to 256 CNs, and where slices of some length are the faster for it:
+        // psgd_min_rows; us a step of long slices, this kernel / launches per chunk: 784-136-10, K = 512
+        // 19.6 / 16.2; 784-384-10, K = 512 43.3 / 43.2, K = 1,024 118 / 91)
         bool fits = H <= PSGD_MAX_H && (H <= 128 || K <= 256) && In <= 4 * MAX_IB * 16 && kg >= 1;
+        if (fits && H > 128) {
+            n->ps_min_rows = psgd_min_rows(H, In, K, (K + kg - 1) / kg, n->pspecial, n->act[1] == PNN_SOFTMAX);
+            fits = n->ps_min_rows > 0;
+        }
         if (fits && hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)n->psmem) != hipSuccess)
             fits = false;
         if (fits && hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, fn, 256, n->psmem) != hipSuccess) fits = false;
@@ -1182,7 +1207,7 @@ pnn_status pnn_init(const pnn_config* cfg, const float* theta0_host, void* hip_s
         }
         if (!fits || H > 128) {
             // launches per chunk: where the persistent kernel does not fit, and above 128 neurons
-            // beside it, for epochs that are recorded into a graph
+            // beside it, for epochs of short slices or recorded into a graph
             n->T = 128;
             while (n->T > 16 && (int64_t)n->T * H > 16384) n->T >>= 1;
         }

@@ -7,7 +7,7 @@ import torch
 import pnn_inputs as I
 from oracle import oracle as O
 from paper_2304_09590_amd import pnn as B
-from tests.parity import BF16_TOL, EPOCH_TOL, assert_close, log
+from tests.parity import BF16_TOL, EPOCH_TOL, assert_close, log, oracle_replicas
 
 pytestmark = pytest.mark.gpu
 
@@ -55,11 +55,46 @@ def train_both(w, N, epochs):
     (dict(sizes=(784, 256, 10), replicas=20), 20 * 40 + 3),   # 32-row tiles
     (dict(sizes=(784, 144, 10), replicas=70), 70 * 34 + 1),   # two launches of 35 CNs
     (dict(sizes=(784, 264, 10), replicas=16), 16 * 40 + 3),   # 32-row tiles, six neurons per lane
-    (dict(sizes=(784, 136, 10), replicas=256), 256 * 3 + 1),  # the most CNs of the persistent launches
+    (dict(sizes=(784, 136, 10), replicas=256), 256 * 130 + 1),  # the most CNs of the persistent launches
     (dict(sizes=(784, 136, 10), replicas=257), 257 * 3 + 1),  # launches per chunk
 ])
 def test_wide_per_sample(over, N):
     train_both(I.WORKLOADS[1].scaled(**over), N, 2).close()
+
+
+def kernels_of_an_epoch(net, X, y):
+    net.profile(True)
+    net.train_epoch(dev(X), dev(y))
+    names = set(net.profile_read())
+    net.profile(False)
+    return names
+
+
+@pytest.mark.parametrize("over,rows,persistent", [
+    (dict(sizes=(784, 256, 10), replicas=2), 100, True),
+    (dict(sizes=(784, 256, 10), replicas=2), 2, False),      # one launch's start-up is more than two steps
+    (dict(sizes=(784, 256, 10), replicas=128), 40, False),   # five launches against all CNs at once
+    (dict(sizes=(784, 256, 10), replicas=128), 100, True),
+    (dict(sizes=(784, 384, 10), replicas=128), 60, False),
+    (dict(sizes=(784, 384, 10), acts=(I.TANH, I.SOFTMAX), loss=I.LOSS_XENT, lr=0.01, replicas=4), 60, True),
+    (dict(sizes=(784, 384, 10), acts=(I.TANH, I.SOFTMAX), loss=I.LOSS_XENT, lr=0.01, replicas=128), 300, False),
+])
+def test_wide_per_sample_short_slices(over, rows, persistent):
+    """Where several persistent launches would follow each other for short slices, or for a slower
+    step than all CNs take together, an epoch takes the launches per chunk; both agree with the oracle."""
+    w = I.WORKLOADS[1].scaled(**over)
+    K = w.replicas
+    X, y = I.train_set(w, K * rows)
+    th0 = I.init_params(w)
+    net = make_net(w, th0)
+    names = kernels_of_an_epoch(net, X, y)
+    assert ("psgd_persistent" in names, "psgd_chunk" in names) == (persistent, not persistent), names
+    o = O.Oracle.from_workload(w)
+    ids = sorted({0, K // 2, K - 1})
+    ref = oracle_replicas(o, np.tile(th0.astype(np.float64), (len(ids), 1)), ids, X, y)
+    for i, k in enumerate(ids):
+        assert_close(w.sizes, net.get_params(k), ref[i], EPOCH_TOL, f"replica {k}")
+    net.close()
 
 
 def first_step_w2(H, act2, b1, b2):
