@@ -221,9 +221,9 @@ int32_t pnn_profile_read(pnn_net* net, const char** names, double* total_ms, int
  *                           update (one pass less over the hidden activations);
  *  "mini-batch"             otherwise: kernel launches per layer and batch step, or, with one
  *                           hidden layer and the other limits of "mini-batch persistent", for
- *                           batches of 33 to 64 rows (while three launches hold the CNs) and for
- *                           bf16-mixed batches of up to 64, the persistent kernel (an epoch that
- *                           is recorded into a graph: launches).
+ *                           batches of 33 to 64 rows and for bf16-mixed batches of up to 64, the
+ *                           persistent kernel where that is faster (few CNs or wide inputs; an epoch
+ *                           that is recorded into a graph: launches).
  * The environment variable PNN_MB_PLAN=launch, read by pnn_init, selects "mini-batch"
  * where the persistent mini-batch kernel or "mini-batch fused last layer" would apply.  The persistent plans' workgroups wait for each
  * other with bounded polls (PNN_SPIN_LIMIT, read by pnn_init, default 4194304 polls); a launch

@@ -837,6 +837,40 @@ const void* mbp_fn_of(int rt, int mt) {
 }
 const void* mbp_fn(bool bf16, int rt, int mt) { return bf16 ? mbp_fn_of<true>(rt, mt) : mbp_fn_of<false>(rt, mt); }
 
+// Whether `groups` persistent launches of rt sub-tiles a workgroup are the faster way to a batch step.
+// fp32 batches of up to 32 rows always are.  The others are while one launch holds all CNs, and behind
+// a hidden layer of at most 16 neurons (the launches per layer update it by one thread a weight).
+// Otherwise the groups' steps follow each other, while a launch per layer takes all CNs at once: its
+// time is a fixed one and the traffic of the weights and rows, which for narrow inputs is little.
+// Estimates of both in us, fitted to 691 measured shapes (32 to 512 neurons behind 16 to 784 inputs, 2
+// to 24 groups; b: the batch, in: the inputs, relative to the widest).  The one taken is more than
+// 10 % slower than the other in 18 of them, 22 % at most.  A step, persistent / per layer: bf16, B = 32:
+// 784-512-10, K = 100 91 / 140, 64-512-10, K = 100 48 / 37, K = 400 240 / 106; fp32, B = 64:
+// 784-512-10, K = 32 64 / 94, 784-64-10, K = 337 111 / 105, 64-256-10, K = 64 35 / 28.
+// Above 32 rows three launches at most (784-256-10, K = 128 129 / 113).
+bool mbp_faster(bool bf16, int B, int rt, int groups, int H, int In, int K) {
+    if (groups == 1 || H <= 16 || (!bf16 && B <= 32)) return true;
+    if (B > 32 && groups > 3) return false;
+    const double in = In / 784.0, b = B / (B <= 32 ? 32.0 : 64.0), k = K / 100.0, kh = (double)K * H / 1e4;
+    const double khin = 1e-2 * kh * In, khb = 1e-2 * kh * B, hb = H / 512.0 * b, rows = 1e-6 * B * In;
+    const double group = (K + groups - 1) / groups;              // CNs of a launch
+    const double tail = H > 256 && B * H < 32768 ? 1.0 : 0.0;    // (the last layer in one workgroup per CN)
+    double step, layers;
+    if (B <= 32) {
+        step = rt == 1 ? 6.2 + 2.7 * in + (0.4 + 1.8 * in) * b : 7.2 + 4.2 * in + (1.4 + 1.4 * in) * b;
+        layers = 13.9 + 2.5 * khin + 2.2 * kh + 0.9 * k + 1.2 * khb + 6.4 * hb + 1.6 * K * rows;
+    } else if (bf16) {
+        step = rt == 1 ? 9.3 + 0.6 * in + (0.6 + 5.5 * in) * b + 0.5 * group * rows
+                       : 9.9 + 9.8 * in + (1.3 + 7.4 * in) * b + 0.7 * group * rows;
+        layers = 18.1 + 6.7 * in + 2.7 * khin + 1.4 * k + 1.4 * khb + 10.7 * hb + 1.2 * K * rows + 5.3 * tail;
+    } else {
+        step = rt == 1 ? 8.5 + 3.6 * in + (1.0 + 3.5 * in) * b + 0.4 * group * rows
+                       : 11.5 + 11.9 * in + (3.9 + 1.9 * in) * b + 0.4 * group * rows;
+        layers = 17.7 + 1.5 * in + 3.3 * khin + 1.6 * kh + 0.7 * k + 4.5 * khb + 7.3 * hb + 1.2 * K * rows + 5.4 * tail;
+    }
+    return groups * step <= layers;
+}
+
 pnn_status mbp_epoch(pnn_net* n, const float* X, const int32_t* Y, int64_t N, hipStream_t s) {
     const int K = n->cfg.replicas;
     {
@@ -1251,11 +1285,7 @@ pnn_status pnn_init(const pnn_config* cfg, const float* theta0_host, void* hip_s
             // fit the CUs, one launch each; the one with the least estimated time (launches x the
             // relative time of a batch step: 1 with 16-neuron tiles, with 32 1.45, or 1.7 in batches
             // of more than 32 rows, as measured with 784-256-10 and 784-512-10 nets).
-            // Above 32 rows at most three launches: a step of the fourth starts where the per-layer
-            // launches, which take all CNs at once, have caught up (784-512-10, B = 64, us a step,
-            // this kernel / launches: K = 32 64 / 94, K = 64 127 / 119; bf16 784-256-10: K = 32
-            // 34 / 50, K = 64 67 / 62; 784-256-10: K = 128 129 / 113).  Up to 32 rows it is the
-            // faster one up to the 256 CNs measured (784-512-10, B = 32, K = 256: 233 / 354).
+            // Where several launches lose to the launches per layer: mbp_faster.
             const int mt = mbp_row_tiles(B);
             int rt = 0, kg = 0;
             double best = 1e30;
@@ -1267,7 +1297,7 @@ pnn_status pnn_init(const pnn_config* cfg, const float* theta0_host, void* hip_s
                 const double cost = (double)((K + g - 1) / g) * (r == 1 ? 1.0 : mt == 2 ? 1.45 : 1.7);
                 if (cost < best) { best = cost; rt = r; kg = g; }
             }
-            if (rt > 0 && (mt == 2 || (K + kg - 1) / kg <= 3)) {
+            if (rt > 0 && mbp_faster(n->bf16, B, rt, (K + kg - 1) / kg, H, n->sizes[0], K)) {
                 const int nrb = (H + 16 * rt - 1) / (16 * rt);
                 const size_t smem = (size_t)mbp_lds_floats(rt, mt) * sizeof(float);
                 const void* fn = mbp_fn(n->bf16, rt, mt);

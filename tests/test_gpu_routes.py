@@ -235,6 +235,36 @@ def test_persistent_mini_batch(over, N, precision):
     net.close()
 
 
+@pytest.mark.parametrize("precision,over,persistent", [
+    (I.BF16_MIXED, dict(sizes=(16, 512, 10), batch=32, replicas=200), False),
+    (I.BF16_MIXED, dict(sizes=(64, 384, 10), batch=24, replicas=200), False),
+    (I.BF16_MIXED, dict(sizes=(256, 384, 10), batch=1, replicas=200), False),
+    (I.BF16_MIXED, dict(sizes=(784, 256, 10), batch=16, replicas=100), True),
+    (I.BF16_MIXED, dict(sizes=(16, 16, 10), batch=16, replicas=600), True),   # three launches of 16 neurons
+    (I.BF16_MIXED, dict(sizes=(64, 64, 10), batch=64, replicas=332), False),
+    (I.FP32, dict(sizes=(16, 256, 10), batch=64, replicas=64), False),
+    (I.FP32, dict(sizes=(784, 384, 10), batch=48, replicas=32), True),
+    (I.FP32, dict(sizes=(16, 512, 10), batch=32, replicas=100), True),        # (up to 32 rows: always)
+])
+def test_persistent_mini_batch_or_launches(over, precision, persistent):
+    """Several persistent launches for a step, or a launch per layer that takes all CNs at once; both
+    agree with the oracle."""
+    w = I.WORKLOADS[2].scaled(precision=precision, **over)
+    K = w.replicas
+    X, y = I.random_batch(w.sizes[0], w.sizes[-1], K * w.batch + 3, 5)
+    th0 = I.init_params(w)
+    net = make_net(w, th0)
+    names = kernels_of_an_epoch(net, X, y)
+    assert ("mb_persistent" in names) == persistent and ("upd_gemm" in names or "upd_gemm_x3" in names) != persistent, names
+    o = O.Oracle.from_workload(w)
+    ids = sorted({0, 2, K // 2, K - 1})
+    ref = oracle_replicas(o, np.tile(th0.astype(np.float64), (len(ids), 1)), ids, X, y)
+    bf16 = precision == I.BF16_MIXED
+    for i, k in enumerate(ids):
+        assert_close(w.sizes, net.get_params(k), ref[i], BF16_TOL if bf16 else EPOCH_TOL, f"replica {k}", layerwise=bf16)
+    net.close()
+
+
 def test_persistent_mini_batch_gives_up_waiting(monkeypatch):
     """(batches above 32 rows and bf16-mixed: a wait that runs into its bound ends the launch; the
     next call reports it)"""
