@@ -395,10 +395,15 @@ pnn_status run_gemm(pnn_net* n, hipStream_t s, const GemmArgs& g, int Z, const c
         // (gemm256x3_kernel)
         if constexpr (A_KC && B_KC && (EPI == EPI_FWD || EPI == EPI_STORE)) {
             // (not where its tiles leave a last round of workgroups emptier than the 128 x 128 tiles,
-            // whose round takes 0.66 of the time: 1,808 rows x 1,024 on 256 CUs 67 -> 45 us)
+            // whose round takes 0.66 of the time: 1,808 rows x 1,024 on 256 CUs 67 -> 45 us; 0.70
+            // for contractions of up to 192 and 0.75 up to 96, of which the epilogue takes the larger
+            // part.  128 x 128 / 128 x 256 tiles in us: 384 columns, 300 rows, 64 CNs (3 / 2 rounds)
+            // behind 64 inputs 39 / 36, behind 192 52 / 53; 640 columns, 200 rows, 100 CNs (4 / 3
+            // rounds) behind 64 56 / 51, behind 128 68 / 64, behind 192 equal.)
             const int64_t t256 = (int64_t)((g.N + 255) / 256) * ((g.M + 127) / 128) * Z;
             const int64_t t128 = (int64_t)((g.N + 127) / 128) * ((g.M + 127) / 128) * Z;
-            const bool fuller = g.zpart != nullptr || (t256 + 255) / 256 <= 0.66 * (double)((t128 + 255) / 256);
+            const double round128 = g.Kd <= 96 ? 0.75 : g.Kd <= 192 ? 0.70 : 0.66;
+            const bool fuller = g.zpart != nullptr || (t256 + 255) / 256 <= round128 * (double)((t128 + 255) / 256);
             if (n->gemm_x3 && g.M >= 128 && g.N >= 256 && fuller && g.shadow == nullptr && g.ksplit == 1 && !(g.sample_dims & 4)) {
                 static const hipError_t attr = hipFuncSetAttribute((const void*)gemm256x3_kernel<EPI>,
                                                                    hipFuncAttributeMaxDynamicSharedMemorySize,

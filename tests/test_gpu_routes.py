@@ -299,6 +299,29 @@ def test_split_forward_and_few_strips(over, N, precision, monkeypatch):
     train_both(I.WORKLOADS[2].scaled(precision=precision, **over), N, 1).close()
 
 
+@pytest.mark.parametrize("over", [
+    dict(sizes=(784, 1024, 10), batch=128, replicas=64),  # 128 x 256 tiles: one round of workgroups
+    dict(sizes=(64, 384, 10), batch=300, replicas=64),    # 128 x 256: two rounds, a short contraction
+    dict(sizes=(784, 384, 10), batch=300, replicas=64),   # 128 x 128: two rounds of the larger would take longer
+])
+def test_split_bf16_forward_of_many_cns(over, monkeypatch):
+    """The split-bf16 forward with the last layer in launches of its own, in tiles of 128 x 256 and of
+    128 x 128, the last batch ragged."""
+    monkeypatch.setenv("PNN_MB_PLAN", "launch")
+    w = I.WORKLOADS[4].scaled(**over)
+    K = w.replicas
+    X, y = I.random_batch(w.sizes[0], w.sizes[-1], K * (w.batch + 5) + 1, 5)
+    th0 = I.init_params(w)
+    net = make_net(w, th0)
+    names = kernels_of_an_epoch(net, X, y)
+    assert {"fwd_gemm_x3", "out_layer", "last_layer"} <= names, names
+    ids = [0, K // 2, K - 1]
+    ref = oracle_replicas(O.Oracle.from_workload(w), np.tile(th0.astype(np.float64), (len(ids), 1)), ids, X, y)
+    for i, k in enumerate(ids):
+        assert_close(w.sizes, net.get_params(k), ref[i], EPOCH_TOL, f"replica {k}")
+    net.close()
+
+
 @pytest.mark.parametrize("precision", [I.FP32, I.BF16_MIXED])
 @pytest.mark.parametrize("sizes,acts,loss,rows", [
     ((784, 128, 10), (I.SIGMOID, I.SIGMOID), I.LOSS_MSE, 1),
