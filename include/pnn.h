@@ -19,6 +19,10 @@
  *    and a pnn_infer call with correct_host != NULL wait for the device.  After a training
  *    epoch on a persistent plan (pnn_plan), the next call that consumes the CNs other than
  *    pnn_train_epoch first waits for that epoch to end, to read its failure flag.
+ *  - pnn_train_epoch, pnn_train_epoch_order, pnn_merge and pnn_infer (without a count) may be
+ *    recorded into a graph, after a call of the same kind with at least as many rows has sized the
+ *    handle's workspace (growth is refused while the stream records: PNN_EHIP, nothing recorded).  The
+ *    graph may be replayed until pnn_destroy, also after later calls with more rows.
  *  - Errors are returned as a pnn_status; the message of the last failure is available
  *    from pnn_last_error (per handle; a NULL handle gives the message of the last failed
  *    pnn_init on the calling thread).  No exception or abort crosses the interface.

@@ -26,6 +26,7 @@
 #include <cstring>
 #include <map>
 #include <mutex>
+#include <set>
 #include <string>
 #include <vector>
 
@@ -145,6 +146,11 @@ struct pnn_net {
     bool abort_pending = false;
     hipEvent_t abort_ev = nullptr;
 
+    // device buffers that calls recorded into a graph use: growth leaves them to the graph's
+    // replays (release), and they are freed with the handle
+    std::set<void*> recorded;
+    std::vector<void*> retired;
+
     // profiling
     bool prof = false;
     std::vector<ProfRec> pending;
@@ -174,6 +180,8 @@ pnn_status fail(pnn_net* n, pnn_status s, const char* fmt, ...) {
             return fail(net, PNN_EHIP, "%s failed: %s", #call, hipGetErrorString(e_));            \
         }                                                                                          \
     } while (0)
+
+#define TRY(x) do { pnn_status st_ = (x); if (st_ != PNN_OK) return st_; } while (0)
 
 int64_t round_up(int64_t v, int64_t m) { return (v + m - 1) / m * m; }
 
@@ -228,6 +236,48 @@ pnn_status dev_alloc(pnn_net* n, T** p, size_t elems) {
     }
     e = hipMemset(*p, 0, elems * sizeof(T));
     if (e != hipSuccess) return fail(n, PNN_EHIP, "hipMemset failed: %s", hipGetErrorString(e));
+    return PNN_OK;
+}
+
+// is the stream recording a graph?
+bool capturing(hipStream_t s) {
+    hipStreamCaptureStatus st = hipStreamCaptureStatusNone;
+    if (hipStreamIsCapturing(s, &st) != hipSuccess) {
+        (void)hipGetLastError();
+        return false;
+    }
+    return st == hipStreamCaptureStatusActive;
+}
+
+// ---------------------------------------------------------------------------------------
+// workspaces that grow with the rows of a call
+
+// a buffer that is about to be replaced: freed, or kept for the graph that has recorded it
+void release(pnn_net* n, void* p) {
+    if (!p) return;
+    if (n->recorded.erase(p)) n->retired.push_back(p);
+    else (void)hipFree(p);
+}
+
+// While a stream records a graph no memory can be had (the runtime refuses it in every capture mode,
+// and ends the recording): a call that needs more is refused before it asks.
+pnn_status no_growth(pnn_net* n) {
+    return fail(n, PNN_EHIP, "the workspace cannot grow while the stream records a graph: run a call of that many rows first");
+}
+
+// at least `need` elements in *buf for a call on stream s
+template <typename T>
+pnn_status grow(pnn_net* n, hipStream_t s, T** buf, size_t* have, size_t need) {
+    const bool rec = capturing(s);
+    if (need > *have) {
+        if (rec) return no_growth(n);
+        release(n, *buf);
+        *buf = nullptr;
+        *have = 0;
+        TRY(dev_alloc(n, buf, need));
+        *have = need;
+    }
+    if (rec) n->recorded.insert(*buf);
     return PNN_OK;
 }
 
@@ -457,8 +507,6 @@ Operand opnd(const void* p, int64_t zs, int64_t ld, int xrows, int64_t xshift = 
     o.ptr = p; o.zstride = zs; o.ld = ld; o.xrows = xrows; o.xshift = xshift;
     return o;
 }
-
-#define TRY(x) do { pnn_status st_ = (x); if (st_ != PNN_OK) return st_; } while (0)
 
 // ---------------------------------------------------------------------------------------
 // mini-batch plan: one batch step of every CN
@@ -732,8 +780,14 @@ int64_t psgd_min_rows(int H, int In, int K, int groups, bool special, bool softm
     return rows > 1e6 ? 0 : std::max<int64_t>(1, (int64_t)rows);
 }
 
-// floats of the Gram blocks of an epoch with slices of nmax rows, in the launches per chunk
-size_t psgd_gram_elems(int K, int64_t nmax, int T) { return (size_t)K * ((nmax + T - 1) / T) * T * T; }
+// floats of the Gram blocks of an epoch with slices of nmax rows: the larger of the two layouts, so
+// that an epoch in the one never grows the buffer that a recorded epoch in the other uses
+size_t psgd_gram_elems(const pnn_net* n, int64_t nmax) {
+    const int PT = psgd_chunk_len(n->sizes[1]), T = n->T;
+    const size_t per = n->persistent ? (size_t)((nmax + PT - 1) / PT) * PT * psgd_gs(PT) : 0;
+    const size_t chunk = T > 0 ? (size_t)((nmax + T - 1) / T) * T * T : 0;
+    return (size_t)n->cfg.replicas * std::max(per, chunk);
+}
 
 // after a persistent launch: its abort flag is read by the next call that consumes the CNs
 pnn_status note_persistent_launch(pnn_net* n, hipStream_t s) {
@@ -748,18 +802,9 @@ pnn_status psgd_persistent_epoch(pnn_net* n, const float* X, const int32_t* Y, i
     const int64_t nmax = shard_len(N, K, 0);
     const int PT = psgd_chunk_len(H);
     const int nch = (int)((nmax + PT - 1) / PT);
-    auto grow = [&](float** buf, size_t* have, size_t need) -> pnn_status {
-        if (need <= *have) return PNN_OK;
-        if (*buf) (void)hipFree(*buf);
-        *buf = nullptr;
-        *have = 0;
-        TRY(dev_alloc(n, buf, need));
-        *have = need;
-        return PNN_OK;
-    };
     const int GS = psgd_gs(PT);  // padded Gram row stride (the kernel's LDS layout)
-    TRY(grow(&n->gram, &n->gram_elems, std::max((size_t)K * nch * PT * GS, n->T > 0 ? psgd_gram_elems(K, nmax, n->T) : 0)));
-    TRY(grow(&n->gramx, &n->gramx_elems, (size_t)K * std::max(nch - 1, 1) * PT * GS));
+    TRY(grow(n, s, &n->gram, &n->gram_elems, psgd_gram_elems(n, nmax)));
+    TRY(grow(n, s, &n->gramx, &n->gramx_elems, (size_t)K * std::max(nch - 1, 1) * PT * GS));
     // (products z = CN * chunks + chunk, in launches of at most 65,535, the grid's limit)
     auto gram_products = [&](GemmArgs& g, int64_t total) -> pnn_status {
         for (int64_t z0 = 0; z0 < total; z0 += 65535) {
@@ -921,16 +966,6 @@ pnn_status mbp_epoch(pnn_net* n, const float* X, const int32_t* Y, int64_t N, hi
     return note_persistent_launch(n, s);
 }
 
-// is the stream recording a graph?
-bool capturing(hipStream_t s) {
-    hipStreamCaptureStatus st = hipStreamCaptureStatusNone;
-    if (hipStreamIsCapturing(s, &st) != hipSuccess) {
-        (void)hipGetLastError();
-        return false;
-    }
-    return st == hipStreamCaptureStatusActive;
-}
-
 pnn_status psgd_epoch(pnn_net* n, const float* X, const int32_t* Y, int64_t N, hipStream_t s) {
     // (above 128 neurons an epoch of short slices, and one recorded into a graph, takes the launches
     // per chunk, whose workspaces those nets keep: a persistent launch is cooperative and its
@@ -939,14 +974,7 @@ pnn_status psgd_epoch(pnn_net* n, const float* X, const int32_t* Y, int64_t N, h
     const int64_t nmax = shard_len(N, K, 0);
     if (n->persistent && !(T > 0 && (nmax < n->ps_min_rows || capturing(s)))) return psgd_persistent_epoch(n, X, Y, N, s);
     const int nch = (int)((nmax + T - 1) / T);
-    const size_t need = psgd_gram_elems(K, nmax, T);
-    if (need > n->gram_elems) {
-        if (n->gram) (void)hipFree(n->gram);
-        n->gram = nullptr;
-        n->gram_elems = 0;
-        TRY(dev_alloc(n, &n->gram, need));
-        n->gram_elems = need;
-    }
+    TRY(grow(n, s, &n->gram, &n->gram_elems, psgd_gram_elems(n, nmax)));
     // Gram matrices of every chunk: G[t][s] = x_t . x_s
     {
         GemmArgs g = gemm_base(n, T, T, In, N, 0, T, 3);
@@ -1042,6 +1070,7 @@ void free_all(pnn_net* n) {
     f(n->theta); f(n->merged); f(n->shadow); f(n->mshadow);
     for (int l = 0; l < 9; ++l) { f(n->act_ws[l]); f(n->del_ws[l]); f(n->inf_ws[l]); }
     f(n->d_correct); f(n->d_cost); f(n->d_cost_sum); f(n->d_mw); f(n->ord_x); f(n->ord_y); f(n->ppart); f(n->d1); f(n->gram); f(n->flags); f(n->qbuf); f(n->gramx); f(n->zpart); f(n->fx3_zpart); f(n->fx3_dout);
+    for (void* p : n->retired) f(p);
     if (n->abort_ev) (void)hipEventDestroy(n->abort_ev);
     for (auto& r : n->pending) { (void)hipEventDestroy(r.a); (void)hipEventDestroy(r.b); }
     for (auto e : n->free_events) (void)hipEventDestroy(e);
@@ -1405,15 +1434,18 @@ pnn_status pnn_train_epoch_order(pnn_net* n, const float* x_dev, const int32_t* 
     if (N > INT32_MAX) return fail(n, PNN_ESHAPE, "N = %lld does not fit the int32 order", (long long)N);
     hipStream_t s = (hipStream_t)hip_stream;
     const int D = n->sizes[0];
+    const bool rec = capturing(s);
     if (N > n->ord_rows) {
+        if (rec) return no_growth(n);
         HIP_TRY(n, hipStreamSynchronize(s));
-        if (n->ord_x) (void)hipFree(n->ord_x);
-        if (n->ord_y) (void)hipFree(n->ord_y);
+        release(n, n->ord_x);
+        release(n, n->ord_y);
         n->ord_x = nullptr; n->ord_y = nullptr; n->ord_rows = 0;
         TRY(dev_alloc(n, &n->ord_x, (size_t)N * D));
         TRY(dev_alloc(n, &n->ord_y, (size_t)N));
         n->ord_rows = N;
     }
+    if (rec) n->recorded.insert({n->ord_x, n->ord_y});
     {
         Launch l(n, s, "gather_rows");
         gather_rows_kernel<<<(unsigned)N, 256, 0, s>>>(x_dev, y_dev, order_dev, N, D, n->ord_x, n->ord_y);
@@ -1484,16 +1516,20 @@ static int64_t noalloc_eval_bytes(const pnn_net* n, int64_t nrows, bool cost) {
 static pnn_status grow_inference_ws(pnn_net* n, int64_t nrows, hipStream_t s) {
     const int L = n->L;
     const int rows = (int)std::min<int64_t>(nrows, INFER_CHUNK);
+    const bool rec = capturing(s);
     if (L > 1 && rows > n->inf_rows) {
+        if (rec) return no_growth(n);
         HIP_TRY(n, hipStreamSynchronize(s));
         const size_t el = n->bf16 ? 2 : 4;
+        n->inf_rows = 0;
         for (int l = 1; l < L; ++l) {
-            if (n->inf_ws[l]) (void)hipFree(n->inf_ws[l]);
+            release(n, n->inf_ws[l]);
             n->inf_ws[l] = nullptr;
             TRY(dev_alloc(n, (char**)&n->inf_ws[l], (size_t)rows * n->sizes[l] * el));
         }
         n->inf_rows = rows;
     }
+    for (int l = 1; rec && l < L; ++l) n->recorded.insert(n->inf_ws[l]);
     return PNN_OK;
 }
 

@@ -201,6 +201,119 @@ def test_epoch_recorded_into_a_graph(idx, over, N):
     net.close()
 
 
+@pytest.mark.parametrize("idx,over,rows", [
+    (1, dict(sizes=(784, 384, 10), replicas=2), (100, 120, 120, 600)),  # (an eager epoch's blocks: 40 floats a row, not 32)
+    (1, dict(sizes=(784, 512, 10), replicas=2), (100, 100, 130, 600)),
+])
+def test_recorded_epoch_outlives_larger_ones(idx, over, rows):
+    """A recorded epoch replayed after epochs of more rows, whose workspace has taken the place of the
+    recorded one's: every replay against the oracle."""
+    w = I.WORKLOADS[idx].scaled(**over)
+    K = w.replicas
+    first, recorded, *later = (K * r for r in rows)
+    X, y = I.train_set(w, K * rows[-1])
+    xd, yd = dev(X), dev(y)
+    th0 = I.init_params(w)
+    net = make_net(w, th0)
+    o = O.Oracle.from_workload(w)
+    ref = o.replicate(th0)
+
+    def eager(n):
+        net.train_epoch(xd[:n], yd[:n])
+        o.train_epoch(ref, X[:n], y[:n], threads=K)
+
+    eager(first)
+    torch.cuda.synchronize()
+    g = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(g):
+        net.train_epoch(xd[:recorded], yd[:recorded])
+    for n in later:
+        eager(n)
+        junk = torch.full((64 << 20,), float("nan"), device="cuda")  # (takes memory that was freed)
+        log(f"replay of {recorded} rows after {n}")
+        g.replay()
+        torch.cuda.synchronize()
+        o.train_epoch(ref, X[:recorded], y[:recorded], threads=K)
+        for k in range(K):
+            assert_close(w.sizes, net.get_params(k), ref[k], EPOCH_TOL, f"replica {k}, after {n} rows")
+        del junk
+    net.close()
+
+
+def test_recorded_calls_keep_their_workspace():
+    """Recorded inference and recorded epochs in a given order, replayed after calls with more rows."""
+    w = I.WORKLOADS[2].scaled(replicas=2)
+    X, y = I.train_set(w, 2 * 300)
+    xd, yd = dev(X), dev(y)
+    th0 = I.init_params(w)
+    net = make_net(w, th0)
+    o = O.Oracle.from_workload(w)
+    ref = o.replicate(th0)
+    small, large = 2 * 70, 2 * 300
+    order = np.random.default_rng(1).permutation(small).astype(np.int32)
+    od, ol = dev(order), dev(np.arange(large, dtype=np.int32))
+    pred = torch.empty(large, dtype=torch.int32, device="cuda")
+    out = torch.empty((small, 10), dtype=torch.float32, device="cuda")
+    net.train_epoch_order(xd[:small], yd[:small], od)
+    o.train_epoch(ref, X[order], y[order], threads=2)
+    net.infer(xd[:small], pred[:small], which=1, out=out)
+    torch.cuda.synchronize()
+    g = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(g):
+        net.train_epoch_order(xd[:small], yd[:small], od)
+        net.infer(xd[:small], pred[:small], which=1, out=out)
+    net.train_epoch_order(xd, yd, ol)
+    o.train_epoch(ref, X, y, threads=2)
+    net.infer(xd, pred, which=0)
+    for e in range(2):
+        junk = torch.full((64 << 20,), float("nan"), device="cuda")
+        log(f"replay {e}")
+        g.replay()
+        torch.cuda.synchronize()
+        o.train_epoch(ref, X[order], y[order], threads=2)
+        for k in range(2):
+            assert_close(w.sizes, net.get_params(k), ref[k], EPOCH_TOL, f"replica {k}, replay {e}")
+        assert np.max(np.abs(out.cpu().numpy() - o.forward(ref[1], X[:small]))) <= EPOCH_TOL
+        del junk
+    net.close()
+
+
+@pytest.mark.parametrize("call", ["epoch", "order", "infer"])
+def test_growth_is_refused_while_recording(call):
+    """A recorded call with more rows than the workspace holds is refused with a message that says
+    what to do; the handle stays usable and its workspace whole."""
+    w = I.WORKLOADS[1].scaled(sizes=(784, 384, 10), replicas=2)
+    X, y = I.train_set(w, 400)
+    xd, yd = dev(X), dev(y)
+    od = dev(np.arange(400, dtype=np.int32))
+    pred = torch.empty(400, dtype=torch.int32, device="cuda")
+    th0 = I.init_params(w)
+    net = make_net(w, th0)
+    o = O.Oracle.from_workload(w)
+    ref = o.replicate(th0)
+    net.train_epoch_order(xd[:40], yd[:40], od[:40])
+    o.train_epoch(ref, X[:40], y[:40], threads=2)
+    net.infer(xd[:40], pred[:40])
+    torch.cuda.synchronize()
+    calls = {"epoch": lambda: net.train_epoch(xd, yd), "order": lambda: net.train_epoch_order(xd, yd, od),
+             "infer": lambda: net.infer(xd, pred)}
+    g = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(g):
+        with pytest.raises(B.PnnError) as ei:
+            calls[call]()
+        net.merge()
+    assert ei.value.status == B.PNN_EHIP and "records a graph" in str(ei.value)
+    g.replay()   # (the recording went on)
+    torch.cuda.synchronize()
+    assert_close(w.sizes, net.get_params(-1), o.merge(ref), EPOCH_TOL, "merged")
+    calls[call]()
+    if call != "infer":
+        o.train_epoch(ref, X, y, threads=2)
+    for k in range(2):
+        assert_close(w.sizes, net.get_params(k), ref[k], EPOCH_TOL, f"replica {k}")
+    net.close()
+
+
 # ------------------------------------------------------------------------------------
 # the persistent mini-batch kernel: 2 or 4 row tiles of 16 per batch, 16- or 32-neuron tiles, fp32 and
 # bf16-mixed; batches at the edges of a row tile and of the range, ragged last batches, input widths
