@@ -206,31 +206,30 @@ int32_t pnn_profile_read(pnn_net* net, const char** names, double* total_ms, int
 /* Name of the training plan that pnn_init chose for the handle (a static string; "" for
  * a NULL handle).  All plans compute the update of pnn_train_epoch and differ only in the
  * order of fp32 roundings:
- *  "per-sample persistent"  B = 1, one hidden layer of <= 128 neurons, sizes[0] <= 832: one
- *                           launch per epoch for each group of CNs whose workgroups fit the
- *                           device at once (all K CNs in one group where they fit);
- *  "per-sample chunked"     B = 1 otherwise; with one hidden layer of <= 384 neurons,
- *                           sizes[0] <= 832 and K <= 256 the chunks of an epoch run in persistent launches as
- *                           above where that is faster (few CNs or long slices; an epoch that is
- *                           recorded into a graph: in launches per chunk);
- *  "mini-batch persistent"  fp32, one hidden layer, 2 <= B <= 32, <= 16 outputs,
- *                           sizes[0] % 16 == 0 and <= 832, H <= 512: one launch per epoch for
- *                           each group of CNs whose ceil(H / 16) (or ceil(H / 32)) tile
- *                           workgroups fit the device at once;
+ *  "per-sample persistent"  fp32, B = 1, one hidden layer, sizes[0] <= 832: one launch per epoch
+ *                           for each group of CNs whose workgroups fit the device at once.  Any
+ *                           number of CNs up to 128 neurons; up to 384 neurons and 256 CNs, where
+ *                           long slices are the faster for it (few groups).  Above 128 neurons an
+ *                           epoch of short slices, or one that is recorded into a graph, runs as in
+ *                           the chunked plan;
+ *  "per-sample chunked"     fp32, B = 1, one hidden layer of <= 1,024 neurons otherwise: kernel
+ *                           launches per chunk of steps, for all CNs at once;
+ *  "mini-batch persistent"  one hidden layer of <= 512 neurons, <= 16 outputs, sizes[0] % 16 == 0
+ *                           and <= 832: one launch per epoch for each group of CNs whose
+ *                           ceil(H / 16) (or ceil(H / 32)) tile workgroups fit the device at once.
+ *                           fp32, 2 <= B <= 32; and fp32 with 33 <= B <= 64 or bf16-mixed with
+ *                           B <= 64, where that is the faster way (few groups or wide inputs).  An
+ *                           epoch that is recorded into a graph runs as in "mini-batch";
  *  "mini-batch fused last layer"  fp32, one hidden layer of >= 256 neurons (a multiple of
  *                           4), B = 128, <= 16 outputs, sizes[0] >= 128 (a multiple of 4),
  *                           the split-bf16 products (not PNN_GEMM=fp32): kernel launches per
  *                           batch step, with the last layer's forward in the hidden layer's
  *                           forward and its hidden errors and update in the hidden layer's
  *                           update (one pass less over the hidden activations);
- *  "mini-batch"             otherwise: kernel launches per layer and batch step, or, with one
- *                           hidden layer and the other limits of "mini-batch persistent", for
- *                           batches of 33 to 64 rows and for bf16-mixed batches of up to 64, the
- *                           persistent kernel where that is faster (few CNs or wide inputs; an epoch
- *                           that is recorded into a graph: launches).
+ *  "mini-batch"             otherwise: kernel launches per layer and batch step.
  * The environment variable PNN_MB_PLAN=launch, read by pnn_init, selects "mini-batch"
- * where the persistent mini-batch kernel or "mini-batch fused last layer" would apply.  The persistent plans' workgroups wait for each
- * other with bounded polls (PNN_SPIN_LIMIT, read by pnn_init, default 4194304 polls); a launch
+ * where "mini-batch persistent" or "mini-batch fused last layer" would apply.  The persistent
+ * plans' workgroups wait for each other with bounded polls (PNN_SPIN_LIMIT, read by pnn_init, default 4194304 polls); a launch
  * that runs into the bound ends every workgroup and leaves the CNs' parameters unspecified.
  * The next call that consumes the CNs -- pnn_merge, pnn_merge_weighted, pnn_infer, pnn_eval,
  * pnn_get_params, pnn_set_params (each waits for the last persistent launch to end first) or

@@ -1706,8 +1706,8 @@ pnn_status pnn_eval_noalloc(pnn_net* n, int32_t which, const float* x_dev, const
 
 const char* pnn_plan(const pnn_net* n) {
     if (!n) return "";
-    if (n->psgd) return n->persistent && n->T == 0 ? "per-sample persistent" : "per-sample chunked";
-    if (n->mbp && !n->bf16 && n->cfg.batch <= 32) return "mini-batch persistent";
+    if (n->psgd) return n->persistent ? "per-sample persistent" : "per-sample chunked";
+    if (n->mbp) return "mini-batch persistent";
     return n->fx3 ? "mini-batch fused last layer" : "mini-batch";
 }
 

@@ -78,14 +78,21 @@ SENSITIVE_FP32_CASES = [
 ]
 
 # ------------------------------------------------------------------------------------
-# the per-sample chunked plan (B = 1, one hidden layer, where the persistent per-sample kernel
-# does not fit): overrides of the 784-128-10 per-sample workload and N, one epoch
+# the per-sample chunked plan (B = 1, one hidden layer, where the persistent per-sample kernel does
+# not fit or would take too many launches), and the persistent plan above 128 neurons: overrides of
+# the 784-128-10 per-sample workload and N, one epoch
 
 CHUNKED_CASES = [
-    # overrides of the 784-128-10 per-sample workload, N; chunk length T = 64 / 128 / 16 / 32
-    (dict(sizes=(784, 256, 10), replicas=2), 2 * 300 + 1),             # 4 full chunks + 44/45
-    (dict(sizes=(784, 160, 10), replicas=48), 48 * 200 + 5),           # 48 CNs: 1 chunk + 72/73
+    # chunk length T = 64 / 32 / 16 / 32; several chunks per CN, the last ones ragged
+    (dict(sizes=(784, 160, 10), acts=(I.SIGMOID, I.SOFTMAX), loss=I.LOSS_XENT, replicas=160), 160 * 70 + 5),
+    (dict(sizes=(784, 512, 10), replicas=2), 2 * 100 + 1),             # 3 chunks + 4/5
     (dict(sizes=(784, 1024, 10), replicas=2), 2 * 50 + 1),             # 3 chunks + 2/3
+    (dict(sizes=(784, 384, 10), acts=(I.SIGMOID, I.SOFTMAX), loss=I.LOSS_XENT, replicas=128), 128 * 40 + 2),
+]
+
+WIDE_PERSISTENT_CASES = [
+    (dict(sizes=(784, 256, 10), replicas=2), 2 * 300 + 1),
+    (dict(sizes=(784, 160, 10), replicas=48), 48 * 200 + 5),
     (dict(sizes=(784, 384, 10), acts=(I.RELU, I.SOFTMAX), loss=I.LOSS_XENT, replicas=3), 3 * 90 + 2),
 ]
 

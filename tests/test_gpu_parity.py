@@ -13,7 +13,8 @@ import pytest
 
 import pnn_inputs as I
 from oracle import oracle as O
-from tests.cases import BF16_ELEMENTWISE, CHUNKED_CASES, EPOCH_CASES, SENSITIVE_FP32_CASES, case_key
+from tests.cases import (BF16_ELEMENTWISE, CHUNKED_CASES, EPOCH_CASES, SENSITIVE_FP32_CASES, WIDE_PERSISTENT_CASES,
+                         case_key)
 from tests.parity import (BF16_TOL, EPOCH_TOL, STEP_TOL, argmax_agrees, assert_close, log, oracle_replicas,
                           rel_err)
 
@@ -148,22 +149,29 @@ def test_epochs(idx, over, N, epochs):
 
 
 # ------------------------------------------------------------------------------------
-# the per-sample chunked plan (B = 1, one hidden layer, where the persistent per-sample kernel
-# does not fit): Gram blocks of each chunk of T samples, the chunk's input sums W1 x_t as one
-# product, the T sequential steps, and the chunk's rank-T update of W1 as one product
+# the per-sample chunked plan (B = 1, one hidden layer, where the persistent per-sample kernel does
+# not fit or would take too many launches): Gram blocks of each chunk of T samples, the chunk's input
+# sums W1 x_t as one product, the T sequential steps, and the chunk's rank-T update of W1 as one
+# product.  The persistent plan above 128 neurons runs the same chunks in one launch, and its epochs of one
+# step in these launches.
+
+ABOVE_128 = [(over, N, "per-sample chunked") for over, N in CHUNKED_CASES] + \
+            [(over, N, "per-sample persistent") for over, N in WIDE_PERSISTENT_CASES]
 
 
-
-@pytest.mark.parametrize("over,N", CHUNKED_CASES)
-def test_chunked_plan_one_step(over, N):
+@pytest.mark.parametrize("over,N,plan", ABOVE_128)
+def test_chunked_plan_one_step(over, N, plan):
     w = I.WORKLOADS[1].scaled(**over)
     K = w.replicas
     X, y = I.train_set(w, K)
     th0 = I.init_params(w)
     net = make_net(w, th0)
-    assert net.plan == "per-sample chunked"
+    assert net.plan == plan
     log(f"chunked one step: {w.name} {over}")
+    net.profile(True)
     net.train_epoch(dev(X), dev(y))
+    assert "psgd_chunk" in net.profile_read()
+    net.profile(False)
     o = O.Oracle.from_workload(w)
     ids = sorted({0, K // 2, K - 1})
     ref = oracle_replicas(o, np.tile(th0.astype(np.float64), (len(ids), 1)), ids, X, y)
@@ -175,17 +183,21 @@ def test_chunked_plan_one_step(over, N):
     net.close()
 
 
-@pytest.mark.parametrize("over,N", CHUNKED_CASES)
-def test_chunked_plan_epoch(over, N):
+@pytest.mark.parametrize("over,N,plan", ABOVE_128)
+def test_chunked_plan_epoch(over, N, plan):
     w = I.WORKLOADS[1].scaled(**over)
     K = w.replicas
     X, y = I.train_set(w, N)
     Xt, yt = I.test_set(w, 2000)
     th0 = I.init_params(w)
     net = make_net(w, th0)
-    assert net.plan == "per-sample chunked"
-    log(f"chunked epoch: {w.name} {over} N={N}")
+    assert net.plan == plan
+    log(f"{plan} epoch: {w.name} {over} N={N}")
+    net.profile(True)
     net.train_epoch(dev(X), dev(y))
+    names = set(net.profile_read())
+    net.profile(False)
+    assert ("psgd_chunk" if plan == "per-sample chunked" else "psgd_persistent") in names, names
     o = O.Oracle.from_workload(w)
     ref = o.replicate(th0)
     o.train_epoch(ref, X, y, threads=8)
@@ -238,12 +250,18 @@ PLAN_CASES = [
     # workload, overrides, plan chosen at init
     (1, {}, "per-sample persistent"),
     (1, dict(replicas=64), "per-sample persistent"),          # 3 launches of 21/21/22 CNs
-    (1, dict(sizes=(784, 256, 10)), "per-sample chunked"),
+    (1, dict(sizes=(784, 256, 10)), "per-sample persistent"),
+    (1, dict(sizes=(784, 256, 10), replicas=257), "per-sample chunked"),
+    (1, dict(sizes=(784, 384, 10), acts=(I.TANH, I.SOFTMAX), loss=I.LOSS_XENT, replicas=128), "per-sample chunked"),
+    (1, dict(sizes=(784, 392, 10)), "per-sample chunked"),
     (2, {}, "mini-batch persistent"),                          # 16 CNs x 16 tiles of 16 neurons
     (2, dict(replicas=20), "mini-batch persistent"),          # 32-neuron tiles
     (2, dict(replicas=40), "mini-batch persistent"),          # 2 launches of 20 CNs
     (2, dict(sizes=(784, 1024, 10)), "mini-batch"),           # 64 tiles of 16 neurons per CN
-    (2, dict(batch=33), "mini-batch"),
+    (2, dict(batch=33), "mini-batch persistent"),
+    (2, dict(batch=65), "mini-batch"),
+    (2, dict(precision=I.BF16_MIXED), "mini-batch persistent"),
+    (2, dict(precision=I.BF16_MIXED, sizes=(64, 384, 10), replicas=200), "mini-batch"),   # 10 launches
     (3, dict(replicas=8), "mini-batch"),                      # bf16, two hidden layers
     (4, dict(replicas=4), "mini-batch fused last layer"),
     (4, dict(sizes=(784, 256, 16), acts=(I.TANH, I.SOFTMAX), loss=I.LOSS_XENT), "mini-batch fused last layer"),

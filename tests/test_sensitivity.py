@@ -22,7 +22,7 @@ import pytest
 
 import pnn_inputs as I
 from oracle import oracle as O
-from tests.cases import BF16_ELEMENTWISE, CHUNKED_CASES, EPOCH_CASES, SENSITIVE_FP32_CASES, case_key
+from tests.cases import BF16_ELEMENTWISE, CHUNKED_CASES, EPOCH_CASES, SENSITIVE_FP32_CASES, WIDE_PERSISTENT_CASES, case_key
 from tests.parity import BF16_TOL, EPOCH_TOL, layer_err, oracle_replicas, rel_err
 
 
@@ -48,7 +48,7 @@ def run(w, theta0, X, y, epochs):
 
 
 FP32_CASES = [c for c in EPOCH_CASES if I.WORKLOADS[c[0]].scaled(**c[1]).precision == I.FP32] + \
-             [(1, over, N, 1) for over, N in CHUNKED_CASES]
+             [(1, over, N, 1) for over, N in CHUNKED_CASES + WIDE_PERSISTENT_CASES]
 
 
 @pytest.mark.parametrize("idx,over,N,epochs", FP32_CASES)
