@@ -112,3 +112,55 @@ BF16_ELEMENTWISE = {
     case_key(3, dict(replicas=8), 8 * 150 + 3, 2): {0: ("W1", "W3", "b3"), 1: ("W3",)},
     case_key(3, dict(replicas=6), 6 * 150 + 5, 1): {0: ("W1", "W3", "b3")},
 }
+
+
+# ------------------------------------------------------------------------------------
+# kernels that a rule on sizes selects (tests/test_gpu_routes.py): overrides of the 784-256-10
+# mini-batch workload and N, two epochs, in both precisions
+
+MB_PERSISTENT_CASES = [
+    # 2 or 4 row tiles of 16 per batch, 16- or 32-neuron tiles; batches at the edges of a row tile and
+    # of the range, ragged last batches, input widths of 1, 49 and 52 blocks of 16 (waves without a
+    # block, with six and with seven), one to 16 tiles
+    (dict(sizes=(784, 256, 10), batch=33, replicas=3), 3 * 100 + 2),
+    (dict(sizes=(784, 256, 10), batch=64, replicas=2), 2 * 130 + 1),      # last batches of 2 and 3 rows
+    (dict(sizes=(784, 256, 10), batch=50, replicas=2), 2 * 150),
+    (dict(sizes=(784, 8, 1), acts=(I.SIGMOID, I.SIGMOID), batch=64, replicas=2), 2 * 96 + 1),
+    (dict(sizes=(832, 136, 16), acts=(I.TANH, I.SOFTMAX), loss=I.LOSS_XENT, batch=49, replicas=2), 2 * 120 + 1),
+    (dict(sizes=(16, 48, 3), batch=48, replicas=3), 3 * 60 + 2),
+    (dict(sizes=(784, 512, 10), batch=40, replicas=3), 3 * 90 + 1),       # 16 tiles of 32 neurons
+    (dict(sizes=(784, 256, 10), batch=64, replicas=18), 18 * 70 + 5),     # 32-neuron tiles, one launch
+    (dict(sizes=(784, 256, 10), batch=36, replicas=40), 40 * 40 + 3),     # several launches
+    (dict(sizes=(784, 64, 10), batch=32, replicas=3), 3 * 70 + 1),
+    (dict(sizes=(784, 56, 10), batch=1, replicas=2), 2 * 20 + 1),         # (fp32: per-sample kernel)
+    (dict(sizes=(784, 256, 10), batch=17, replicas=33), 33 * 40 + 3),     # 2 launches in all widths
+]
+
+SPLIT_FORWARD_CASES = [
+    (dict(sizes=(784, 136, 10), batch=100, replicas=2), 2 * 150 + 1),
+    (dict(sizes=(784, 256, 10), batch=129, replicas=3), 3 * 140 + 2),
+    (dict(sizes=(784, 200, 104, 10), acts=(I.TANH, I.SIGMOID, I.SIGMOID), batch=70, replicas=3), 3 * 100 + 1),
+    (dict(sizes=(8, 24, 16, 2), acts=(I.TANH, I.SIGMOID, I.SIGMOID), batch=65, replicas=2), 2 * 70 + 1),
+    (dict(sizes=(784, 256, 10), batch=100, replicas=72), 72 * 100 + 3),   # 32 x 32 tiles beyond the rule
+]
+
+LAST_LAYER_CASES = [
+    # widths that are no multiple of 16 or 64, one and 16 outputs, batches of one staged block, one row
+    # more and several, CNs whose last step has no rows
+    (dict(sizes=(784, 104, 10), batch=100, replicas=3), 3 * 130 + 1),
+    (dict(sizes=(784, 8, 1), acts=(I.SIGMOID, I.SIGMOID), batch=128, replicas=2), 2 * 140),
+    (dict(sizes=(784, 1024, 16), acts=(I.TANH, I.SOFTMAX), loss=I.LOSS_XENT, batch=129, replicas=2), 2 * 129 + 1),
+    (dict(sizes=(784, 272, 10), batch=300, replicas=2), 2 * 301 + 1),
+    (dict(sizes=(784, 64, 512, 10), acts=(I.TANH, I.SIGMOID, I.SIGMOID), batch=72, replicas=8), 8 * 80 + 3),
+    # (bf16: behind it both wide layers' updates in one launch)
+    (dict(sizes=(784, 64, 512, 10), acts=(I.TANH, I.SIGMOID, I.SIGMOID), batch=64, replicas=8), 8 * 80 + 3),
+]
+
+TAIL_CASES = [
+    # one workgroup per CN: up to 256, 512 and 1,024 neurons, batches below the rule and many CNs
+    (dict(sizes=(784, 256, 10), batch=31, replicas=2), 2 * 40 + 1),
+    (dict(sizes=(784, 512, 10), batch=16, replicas=3), 3 * 40 + 1),
+    (dict(sizes=(784, 1024, 10), batch=31, replicas=2), 2 * 40 + 1),
+    (dict(sizes=(64, 512, 10), acts=(I.TANH, I.SOFTMAX), loss=I.LOSS_XENT, batch=70, replicas=129), 129 * 75 + 1),
+]
+ROUTE_CASES = MB_PERSISTENT_CASES + SPLIT_FORWARD_CASES + LAST_LAYER_CASES + TAIL_CASES

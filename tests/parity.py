@@ -17,6 +17,9 @@ are compared normwise per layer, W_l and b_l together:
 the tensors that stay below half the bar elementwise (tests/cases.py) are still compared
 elementwise, and every single step of those nets is held elementwise by tests that restart the
 oracle from the GPU's state before each step.
+
+A few steps move many layers by less than 2e-2 of their parameters, so the tests of single kernels
+(tests/test_gpu_routes.py) also compare what training added to the start (assert_trained).
 """
 from __future__ import annotations
 
@@ -37,6 +40,7 @@ from oracle import oracle as O  # noqa: E402
 STEP_TOL = 1e-5
 EPOCH_TOL = 1e-3
 BF16_TOL = 2e-2
+UPDATE_TOL = {I.FP32: 1e-3, I.BF16_MIXED: 1e-2}
 
 
 def log(msg: str) -> None:
@@ -79,6 +83,15 @@ def assert_close(sizes, got, ref, tol, what="", layerwise=False):
     assert np.all(np.isfinite(got)), f"{what}: non-finite GPU parameters"
     assert worst <= tol, f"{what}: relative error {e} exceeds {tol}"
     return worst
+
+
+def assert_trained(w, got, ref, theta0, what=""):
+    """What training added to theta0, normwise per layer: ||(gpu - theta0) - (ref - theta0)|| <= tol
+    ||ref - theta0||, tol 1e-3 in fp32 and 1e-2 in bf16-mixed precision (the oracle's own update moves
+    by at most 2.1e-3 of itself when its start moves by one fp32 ulp: tests/test_sensitivity.py).
+    A layer that was not trained at all is off by 1."""
+    return assert_close(w.sizes, np.asarray(got, np.float64) - theta0, np.asarray(ref, np.float64) - theta0,
+                        UPDATE_TOL[w.precision], f"{what}, update", layerwise=True)
 
 
 def oracle_replicas(o: O.Oracle, thetas: np.ndarray, ids: Sequence[int], X, y, threads: int = 8) -> np.ndarray:

@@ -285,7 +285,7 @@ def test_plan_selection(idx, over, plan, monkeypatch):
 @pytest.mark.parametrize("idx,over,N,epochs", [
     (2, {}, 16 * 100 + 5, 2),
     (2, dict(sizes=(784, 56, 10), acts=(I.SIGMOID, I.SIGMOID), batch=7, replicas=5), 5 * 40 + 3, 1),
-    (4, dict(replicas=4), 4 * 224 + 2, 1),     # the separate last-layer kernel behind the split-bf16 products
+    (4, dict(replicas=4), 4 * 224 + 2, 1),     # the last layer in two kernels, the products split over waves
 ])
 def test_epochs_launch_plan(idx, over, N, epochs, monkeypatch):
     """The per-layer launch plan on nets that would otherwise get the persistent mini-batch

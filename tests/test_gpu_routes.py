@@ -7,7 +7,8 @@ import torch
 import pnn_inputs as I
 from oracle import oracle as O
 from paper_2304_09590_amd import pnn as B
-from tests.parity import BF16_TOL, EPOCH_TOL, assert_close, log, oracle_replicas
+from tests.cases import LAST_LAYER_CASES, MB_PERSISTENT_CASES, SPLIT_FORWARD_CASES, TAIL_CASES
+from tests.parity import BF16_TOL, EPOCH_TOL, assert_close, assert_trained, log, oracle_replicas
 
 pytestmark = pytest.mark.gpu
 
@@ -23,7 +24,8 @@ def make_net(w, th0):
 def train_both(w, N, epochs):
     """Every CN of `epochs` epochs on the GPU against the oracle's: elementwise in fp32, normwise per
     layer in bf16-mixed precision (where one-ulp differences of the start reach the elementwise
-    bar)."""
+    bar), and what the epochs added to the start normwise per layer in both.  The network, and the
+    launches of each kernel that ran."""
     X, y = I.train_set(w, N) if w.sizes[0] == 784 else I.random_batch(w.sizes[0], w.sizes[-1], N, 5)
     if w.sizes[-1] < 10:
         y = y % w.sizes[-1]
@@ -34,32 +36,43 @@ def train_both(w, N, epochs):
     o = O.Oracle.from_workload(w)
     ref = o.replicate(th0)
     xd, yd = dev(X), dev(y)
+    net.profile(True)
     for _ in range(epochs):
         net.train_epoch(xd, yd)
         o.train_epoch(ref, X, y, threads=8)
+    ran = {name: launches for name, (_, launches) in net.profile_read().items()}
+    net.profile(False)
     for k in range(w.replicas):
-        assert_close(w.sizes, net.get_params(k), ref[k], BF16_TOL if bf16 else EPOCH_TOL, f"replica {k}", layerwise=bf16)
-    return net
+        got = net.get_params(k)
+        assert_close(w.sizes, got, ref[k], BF16_TOL if bf16 else EPOCH_TOL, f"replica {k}", layerwise=bf16)
+        assert_trained(w, got, ref[k], th0, f"replica {k}")
+    return net, ran
 
 
 # ------------------------------------------------------------------------------------
 # per-sample SGD with 129 to 384 hidden neurons: chunks of 32 steps in one persistent launch,
 # 4 or 6 neurons per lane; 16- and 32-row tiles; slices that end at, before and after a chunk
 
-@pytest.mark.parametrize("over,N", [
-    (dict(sizes=(784, 136, 10), replicas=1), 1),
-    (dict(sizes=(784, 136, 10), replicas=2), 2 * 32),
-    (dict(sizes=(784, 256, 10), replicas=3), 3 * 33 + 2),
-    (dict(sizes=(784, 264, 16), acts=(I.RELU, I.SOFTMAX), loss=I.LOSS_XENT, lr=0.01, replicas=2), 2 * 65 + 1),
-    (dict(sizes=(784, 384, 1), replicas=2), 2 * 31),
-    (dict(sizes=(784, 256, 10), replicas=20), 20 * 40 + 3),   # 32-row tiles
-    (dict(sizes=(784, 144, 10), replicas=70), 70 * 34 + 1),   # two launches of 35 CNs
-    (dict(sizes=(784, 264, 10), replicas=16), 16 * 40 + 3),   # 32-row tiles, six neurons per lane
-    (dict(sizes=(784, 136, 10), replicas=256), 256 * 130 + 1),  # the most CNs of the persistent launches
-    (dict(sizes=(784, 136, 10), replicas=257), 257 * 3 + 1),  # launches per chunk
+@pytest.mark.parametrize("over,N,kernel", [
+    (dict(sizes=(784, 136, 10), replicas=1), 1, "psgd_chunk"),
+    (dict(sizes=(784, 136, 10), replicas=2), 2 * 32, "psgd_persistent"),
+    (dict(sizes=(784, 256, 10), replicas=3), 3 * 33 + 2, "psgd_persistent"),
+    (dict(sizes=(784, 264, 16), acts=(I.RELU, I.SOFTMAX), loss=I.LOSS_XENT, lr=0.01, replicas=2), 2 * 65 + 1,
+     "psgd_persistent"),
+    (dict(sizes=(784, 384, 1), replicas=2), 2 * 31, "psgd_persistent"),
+    (dict(sizes=(784, 256, 10), replicas=20), 20 * 40 + 3, "psgd_persistent"),    # 32-row tiles
+    (dict(sizes=(784, 144, 10), replicas=70), 70 * 34 + 1, "psgd_persistent"),    # two launches of 35 CNs
+    (dict(sizes=(784, 264, 10), replicas=16), 16 * 40 + 3, "psgd_persistent"),    # 32-row tiles, six neurons per lane
+    (dict(sizes=(784, 136, 10), replicas=256), 256 * 130 + 1, "psgd_persistent"), # the most CNs of the persistent launches
+    (dict(sizes=(784, 136, 10), replicas=257), 257 * 3 + 1, "psgd_chunk"),
+    (dict(sizes=(840, 128, 10), replicas=2), 2 * 300 + 1, "psgd_chunk"),          # chunks of 128 steps (wide inputs)
+    (dict(sizes=(784, 256, 10), replicas=257), 257 * 70 + 1, "psgd_chunk"),       # of 64
+    (dict(sizes=(784, 392, 10), replicas=2), 2 * 70 + 1, "psgd_chunk"),           # of 32
 ])
-def test_wide_per_sample(over, N):
-    train_both(I.WORKLOADS[1].scaled(**over), N, 2).close()
+def test_wide_per_sample(over, N, kernel):
+    net, ran = train_both(I.WORKLOADS[1].scaled(**over), N, 2)
+    assert kernel in ran and {"psgd_chunk": "psgd_persistent", "psgd_persistent": "psgd_chunk"}[kernel] not in ran, ran
+    net.close()
 
 
 def kernels_of_an_epoch(net, X, y):
@@ -149,7 +162,9 @@ def test_wide_per_sample_activations_at_the_ends_of_the_range():
 def test_wide_per_sample_late_tiles(monkeypatch):
     """Half of the tile workgroups start late: the sequential workgroup waits for every tile."""
     monkeypatch.setenv("PNN_TEST_TILE_DELAY", "2000")
-    train_both(I.WORKLOADS[1].scaled(sizes=(784, 256, 10), replicas=2), 2 * 100 + 1, 2).close()
+    net, ran = train_both(I.WORKLOADS[1].scaled(sizes=(784, 256, 10), replicas=2), 2 * 100 + 1, 2)
+    assert "psgd_persistent" in ran
+    net.close()
 
 
 def test_wide_per_sample_gives_up_waiting(monkeypatch):
@@ -315,28 +330,15 @@ def test_growth_is_refused_while_recording(call):
 
 
 # ------------------------------------------------------------------------------------
-# the persistent mini-batch kernel: 2 or 4 row tiles of 16 per batch, 16- or 32-neuron tiles, fp32 and
-# bf16-mixed; batches at the edges of a row tile and of the range, ragged last batches, input widths
-# of 1, 49 and 52 blocks of 16 (waves without a block, with six and with seven), one to 16 tiles
+# the persistent mini-batch kernel
 
 @pytest.mark.parametrize("precision", [I.FP32, I.BF16_MIXED])
-@pytest.mark.parametrize("over,N", [
-    (dict(sizes=(784, 256, 10), batch=33, replicas=3), 3 * 100 + 2),
-    (dict(sizes=(784, 256, 10), batch=64, replicas=2), 2 * 130 + 1),      # last batches of 2 and 3 rows
-    (dict(sizes=(784, 256, 10), batch=50, replicas=2), 2 * 150),
-    (dict(sizes=(784, 8, 1), acts=(I.SIGMOID, I.SIGMOID), batch=64, replicas=2), 2 * 96 + 1),
-    (dict(sizes=(832, 136, 16), acts=(I.TANH, I.SOFTMAX), loss=I.LOSS_XENT, batch=49, replicas=2), 2 * 120 + 1),
-    (dict(sizes=(16, 48, 3), batch=48, replicas=3), 3 * 60 + 2),
-    (dict(sizes=(784, 512, 10), batch=40, replicas=3), 3 * 90 + 1),       # 16 tiles of 32 neurons
-    (dict(sizes=(784, 256, 10), batch=64, replicas=18), 18 * 70 + 5),     # 32-neuron tiles, one launch
-    (dict(sizes=(784, 256, 10), batch=36, replicas=40), 40 * 40 + 3),     # two launches of 20 CNs
-    (dict(sizes=(784, 64, 10), batch=32, replicas=3), 3 * 70 + 1),
-    (dict(sizes=(784, 56, 10), batch=1, replicas=2), 2 * 20 + 1),         # (fp32: per-sample kernel)
-    (dict(sizes=(784, 256, 10), batch=17, replicas=33), 33 * 40 + 3),     # 2 launches in all widths
-])
+@pytest.mark.parametrize("over,N", MB_PERSISTENT_CASES)
 def test_persistent_mini_batch(over, N, precision):
     w = I.WORKLOADS[2].scaled(precision=precision, **over)
-    net = train_both(w, N, 2)
+    net, ran = train_both(w, N, 2)
+    assert ("psgd_persistent" if w.batch == 1 and precision == I.FP32 else "mb_persistent") in ran, ran
+    assert not {"fwd_gemm", "fwd_gemm_x3", "tail", "out_layer"} & set(ran), ran
     if precision == I.BF16_MIXED:
         # the operand copy of the weights was refreshed: an evaluation of a CN (which reads it)
         # agrees with the oracle's forward of the CN's parameters
@@ -374,7 +376,9 @@ def test_persistent_mini_batch_or_launches(over, precision, persistent):
     ref = oracle_replicas(o, np.tile(th0.astype(np.float64), (len(ids), 1)), ids, X, y)
     bf16 = precision == I.BF16_MIXED
     for i, k in enumerate(ids):
-        assert_close(w.sizes, net.get_params(k), ref[i], BF16_TOL if bf16 else EPOCH_TOL, f"replica {k}", layerwise=bf16)
+        got = net.get_params(k)
+        assert_close(w.sizes, got, ref[i], BF16_TOL if bf16 else EPOCH_TOL, f"replica {k}", layerwise=bf16)
+        assert_trained(w, got, ref[i], th0, f"replica {k}")
     net.close()
 
 
@@ -400,22 +404,21 @@ def test_persistent_mini_batch_gives_up_waiting(monkeypatch):
 # rows and widths at the edges of their tiles, contractions of 1 to 52 blocks
 
 @pytest.mark.parametrize("precision", [I.FP32, I.BF16_MIXED])
-@pytest.mark.parametrize("over,N", [
-    (dict(sizes=(784, 136, 10), batch=100, replicas=2), 2 * 150 + 1),
-    (dict(sizes=(784, 256, 10), batch=129, replicas=3), 3 * 140 + 2),
-    (dict(sizes=(784, 200, 104, 10), acts=(I.TANH, I.SIGMOID, I.SIGMOID), batch=70, replicas=3), 3 * 100 + 1),
-    (dict(sizes=(8, 24, 16, 2), acts=(I.TANH, I.SIGMOID, I.SIGMOID), batch=65, replicas=2), 2 * 70 + 1),
-    (dict(sizes=(784, 256, 10), batch=100, replicas=72), 72 * 100 + 3),   # 32 x 32 tiles beyond the rule
-])
+@pytest.mark.parametrize("over,N", SPLIT_FORWARD_CASES)
 def test_split_forward_and_few_strips(over, N, precision, monkeypatch):
     monkeypatch.setenv("PNN_MB_PLAN", "launch")
-    train_both(I.WORKLOADS[2].scaled(precision=precision, **over), N, 1).close()
+    net, ran = train_both(I.WORKLOADS[2].scaled(precision=precision, **over), N, 1)
+    # (the update on the split-bf16 products with more than 128 strips, and with more than 128 samples)
+    x3 = precision == I.FP32 and (over["replicas"] == 72 or over["batch"] == 129)
+    assert "fwd_gemm" in ran and "fwd_gemm_x3" not in ran and ("upd_gemm_x3" in ran) == x3, ran
+    net.close()
 
 
 @pytest.mark.parametrize("over", [
     dict(sizes=(784, 1024, 10), batch=128, replicas=64),  # 128 x 256 tiles: one round of workgroups
     dict(sizes=(64, 384, 10), batch=300, replicas=64),    # 128 x 256: two rounds, a short contraction
     dict(sizes=(784, 384, 10), batch=300, replicas=64),   # 128 x 128: two rounds of the larger would take longer
+    dict(sizes=(784, 1024, 10), batch=128, replicas=17),  # 128 x 128 in one round; the update in strips
 ])
 def test_split_bf16_forward_of_many_cns(over, monkeypatch):
     """The split-bf16 forward with the last layer in launches of its own, in tiles of 128 x 256 and of
@@ -431,7 +434,18 @@ def test_split_bf16_forward_of_many_cns(over, monkeypatch):
     ids = [0, K // 2, K - 1]
     ref = oracle_replicas(O.Oracle.from_workload(w), np.tile(th0.astype(np.float64), (len(ids), 1)), ids, X, y)
     for i, k in enumerate(ids):
-        assert_close(w.sizes, net.get_params(k), ref[i], EPOCH_TOL, f"replica {k}")
+        got = net.get_params(k)
+        assert_close(w.sizes, got, ref[i], EPOCH_TOL, f"replica {k}")
+        assert_trained(w, got, ref[i], th0, f"replica {k}")
+    net.close()
+
+
+@pytest.mark.parametrize("batch", [50, 96])
+def test_update_strips_of_short_batches(batch, monkeypatch):
+    """The weight update in strips of 128 rows with at most 96 samples (three k-chunks or fewer)."""
+    monkeypatch.setenv("PNN_MB_PLAN", "launch")
+    net, ran = train_both(I.WORKLOADS[2].scaled(batch=batch, replicas=72), 72 * (batch + 3) + 1, 1)
+    assert "upd_gemm_x3" in ran, ran
     net.close()
 
 
@@ -500,18 +514,25 @@ def test_inference_of_not_a_number():
 
 
 # ------------------------------------------------------------------------------------
-# the last layer in two kernels (errors by row, then hidden errors and update by columns): widths that
-# are no multiple of 16 or 64, one and 16 outputs, batches of one staged block, one row more and
-# several, CNs whose last step has no rows
+# the last layer in two kernels (errors by row, then hidden errors and update by columns), and in one
+# workgroup per CN
 
 @pytest.mark.parametrize("precision", [I.FP32, I.BF16_MIXED])
-@pytest.mark.parametrize("over,N", [
-    (dict(sizes=(784, 104, 10), batch=100, replicas=3), 3 * 130 + 1),
-    (dict(sizes=(784, 8, 1), acts=(I.SIGMOID, I.SIGMOID), batch=128, replicas=2), 2 * 140),
-    (dict(sizes=(784, 1024, 16), acts=(I.TANH, I.SOFTMAX), loss=I.LOSS_XENT, batch=129, replicas=2), 2 * 129 + 1),
-    (dict(sizes=(784, 272, 10), batch=300, replicas=2), 2 * 301 + 1),
-    (dict(sizes=(784, 64, 512, 10), acts=(I.TANH, I.SIGMOID, I.SIGMOID), batch=72, replicas=8), 8 * 80 + 3),
-])
+@pytest.mark.parametrize("over,N", LAST_LAYER_CASES)
 def test_last_layer_in_two_kernels(over, N, precision, monkeypatch):
     monkeypatch.setenv("PNN_MB_PLAN", "launch")
-    train_both(I.WORKLOADS[2].scaled(precision=precision, **over), N, 2).close()
+    w = I.WORKLOADS[2].scaled(precision=precision, **over)
+    net, ran = train_both(w, N, 2)
+    assert {"out_layer", "last_layer"} <= set(ran) and "tail" not in ran, ran
+    if precision == I.BF16_MIXED and len(w.sizes) == 4:   # (up to 64 rows both wide layers in one launch)
+        assert ran["upd_gemm"] == ran["last_layer"] * (1 if w.batch <= 64 else 2), ran
+    net.close()
+
+
+@pytest.mark.parametrize("precision", [I.FP32, I.BF16_MIXED])
+@pytest.mark.parametrize("over,N", TAIL_CASES)
+def test_last_layer_in_one_workgroup_per_cn(over, N, precision, monkeypatch):
+    monkeypatch.setenv("PNN_MB_PLAN", "launch")
+    net, ran = train_both(I.WORKLOADS[2].scaled(precision=precision, **over), N, 2)
+    assert "tail" in ran and "last_layer" not in ran, ran
+    net.close()

@@ -15,15 +15,18 @@ theta0 and from theta0 with every value moved by one fp32 ulp (seeded signs), an
   the bar for some seed (so it is compared normwise only); every layer stays below a tenth of
   the bar normwise;
 * the bf16-mixed workload at full size (784-512-256-10, one CN, one 3,750-row epoch): every
-  weight tensor reaches half the bar elementwise, every layer stays below a fifth of it normwise.
+  weight tensor reaches half the bar elementwise, every layer stays below a fifth of it normwise;
+* the cases of single kernels: the update that two epochs add moves by less than a quarter of its
+  bar (1e-3 in fp32, 1e-2 in bf16-mixed precision, of its own norm per layer).
 """
 import numpy as np
 import pytest
 
 import pnn_inputs as I
 from oracle import oracle as O
-from tests.cases import BF16_ELEMENTWISE, CHUNKED_CASES, EPOCH_CASES, SENSITIVE_FP32_CASES, WIDE_PERSISTENT_CASES, case_key
-from tests.parity import BF16_TOL, EPOCH_TOL, layer_err, oracle_replicas, rel_err
+from tests.cases import (BF16_ELEMENTWISE, CHUNKED_CASES, EPOCH_CASES, ROUTE_CASES, SENSITIVE_FP32_CASES,
+                         WIDE_PERSISTENT_CASES, case_key)
+from tests.parity import BF16_TOL, EPOCH_TOL, UPDATE_TOL, layer_err, oracle_replicas, rel_err
 
 
 def one_ulp(theta0: np.ndarray, seed: int) -> np.ndarray:
@@ -121,3 +124,20 @@ def test_bf16_full_size_epoch_is_chaotic_elementwise():
     lay = [layer_err(w.sizes, r[i], r[0]) for i in (1, 2)]
     assert max(max(li.values()) for li in lay) < BF16_TOL / 5, lay
     assert ln == 3750 and st == 0
+
+
+@pytest.mark.parametrize("precision", [I.FP32, I.BF16_MIXED])
+@pytest.mark.parametrize("over,N", ROUTE_CASES)
+def test_update_bar_is_above_the_oracles_own_sensitivity(over, N, precision):
+    w = I.WORKLOADS[2].scaled(precision=precision, **over)
+    X, y = I.train_set(w, N) if w.sizes[0] == 784 else I.random_batch(w.sizes[0], w.sizes[-1], N, 5)
+    y = y % w.sizes[-1]
+    th0 = I.init_params(w).astype(np.float64)
+    th1 = one_ulp(th0, 0)
+    ids = sorted({0, w.replicas // 2, w.replicas - 1})
+    o = O.Oracle.from_workload(w)
+    a, b = (np.tile(t, (len(ids), 1)) for t in (th0, th1))
+    for _ in range(2):
+        a, b = (oracle_replicas(o, t, ids, X, y) for t in (a, b))
+    worst = max(max(layer_err(w.sizes, b[i] - th1, a[i] - th0).values()) for i in range(len(ids)))
+    assert worst <= UPDATE_TOL[precision] / 4, worst
