@@ -2200,10 +2200,12 @@ __global__ __launch_bounds__(256) void out_layer_kernel(RowArgs a) {
         const int r = min(row0 + l16, valid - 1);
         const TX* x = (const TX*)a.x + (a.x_xrows ? (size_t)(d0 + r) * a.x_ld : (size_t)zi * a.x_z + (size_t)r * a.x_ld);
         const TW* W = (const TW*)a.w + (size_t)zi * a.w_z + (size_t)min(l16, a.O - 1) * a.H;
-        constexpr int PF = 4;  // blocks in flight, each with a chain of sums of its own
-        f4 acc[PF];
+        constexpr int PF = 4;  // blocks in flight; every instruction of a block has a chain of sums of its own
+        f4 acc[PF][4];
 #pragma unroll
-        for (int p = 0; p < PF; ++p) acc[p] = f4{0.f, 0.f, 0.f, 0.f};
+        for (int p = 0; p < PF; ++p)
+#pragma unroll
+            for (int q = 0; q < 4; ++q) acc[p][q] = f4{0.f, 0.f, 0.f, 0.f};
         // a block of 16 along H: this lane's four values of the row and of the output's weights
         // (past H: the row's first values against zero weights)
         auto load = [&](int h0, float4& xv, float4& wv) {
@@ -2222,14 +2224,19 @@ __global__ __launch_bounds__(256) void out_layer_kernel(RowArgs a) {
             for (int p = 0; p < PF; ++p) load(h0 + 64 * p, xv[p], wv[p]);
 #pragma unroll
             for (int p = 0; p < PF; ++p) {
-                acc[p] = __builtin_amdgcn_mfma_f32_16x16x4f32(xv[p].x, wv[p].x, acc[p], 0, 0, 0);
-                acc[p] = __builtin_amdgcn_mfma_f32_16x16x4f32(xv[p].y, wv[p].y, acc[p], 0, 0, 0);
-                acc[p] = __builtin_amdgcn_mfma_f32_16x16x4f32(xv[p].z, wv[p].z, acc[p], 0, 0, 0);
-                acc[p] = __builtin_amdgcn_mfma_f32_16x16x4f32(xv[p].w, wv[p].w, acc[p], 0, 0, 0);
+                acc[p][0] = __builtin_amdgcn_mfma_f32_16x16x4f32(xv[p].x, wv[p].x, acc[p][0], 0, 0, 0);
+                acc[p][1] = __builtin_amdgcn_mfma_f32_16x16x4f32(xv[p].y, wv[p].y, acc[p][1], 0, 0, 0);
+                acc[p][2] = __builtin_amdgcn_mfma_f32_16x16x4f32(xv[p].z, wv[p].z, acc[p][2], 0, 0, 0);
+                acc[p][3] = __builtin_amdgcn_mfma_f32_16x16x4f32(xv[p].w, wv[p].w, acc[p][3], 0, 0, 0);
             }
         }
 #pragma unroll
-        for (int i = 0; i < 4; ++i) part[wave][4 * g + i][l16] = (acc[0][i] + acc[1][i]) + (acc[2][i] + acc[3][i]);
+        for (int i = 0; i < 4; ++i) {
+            float s[PF];
+#pragma unroll
+            for (int p = 0; p < PF; ++p) s[p] = (acc[p][0][i] + acc[p][1][i]) + (acc[p][2][i] + acc[p][3][i]);
+            part[wave][4 * g + i][l16] = (s[0] + s[1]) + (s[2] + s[3]);
+        }
     }
     __syncthreads();
     const int rr = tid >> 4, o = tid & 15, row = row0 + rr;
