@@ -3963,6 +3963,16 @@ __device__ __attribute__((always_inline)) inline void psgd_tile(const PsgdPArgs&
                 W[r][j][q] = (ib < nib && h < H && i < In) ? th[a.off_w1 + (size_t)h * In + i] : 0.f;
             }
     }
+    // (chunks of 32 steps: what each update's rounding dropped, carried into the next one -- W1 is
+    // rounded twice as often as with chunks of 64)
+    constexpr bool CARRY = T == 32;
+    float C[CARRY ? RT : 1][MAX_IB][4];
+#pragma unroll
+    for (int r = 0; r < (CARRY ? RT : 1); ++r)
+#pragma unroll
+        for (int j = 0; j < MAX_IB; ++j)
+#pragma unroll
+            for (int q = 0; q < 4; ++q) C[r][j][q] = 0.f;
     const int64_t nz = shard_len(a.n_total, K, k), xs = shard_start(a.n_total, K, k);
     const int nchk = (int)((nz + T - 1) / T);
     int* dready = a.flags + 2 * K + k;
@@ -4054,7 +4064,15 @@ __device__ __attribute__((always_inline)) inline void psgd_tile(const PsgdPArgs&
 #pragma unroll
                 for (int u = 0; u < T / 4; ++u) dacc = __builtin_amdgcn_mfma_f32_16x16x4f32(av[u], bv[r][u], dacc, 0, 0, 0);
 #pragma unroll
-                for (int q = 0; q < 4; ++q) W[r][j][q] -= a.lr * dacc[q];
+                for (int q = 0; q < 4; ++q) {
+                    if constexpr (CARRY) {
+                        const float d = __builtin_fmaf(-a.lr, dacc[q], -C[r][j][q]), w = W[r][j][q] + d;
+                        C[r][j][q] = (w - W[r][j][q]) - d;
+                        W[r][j][q] = w;
+                    } else {
+                        W[r][j][q] -= a.lr * dacc[q];
+                    }
+                }
             }
         }
     };

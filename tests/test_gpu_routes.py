@@ -159,6 +159,38 @@ def test_wide_per_sample_activations_at_the_ends_of_the_range():
     assert np.isnan(first_step_w2(256, I.SIGMOID, b1, np.zeros(2, np.float32))).all()
 
 
+@pytest.mark.parametrize("over", [dict(sizes=(784, 256, 10), replicas=4),
+                                  dict(sizes=(784, 136, 10), replicas=20),   # 32-row tiles
+                                  dict(sizes=(784, 384, 10), acts=(I.TANH, I.SOFTMAX), loss=I.LOSS_XENT, lr=0.005, replicas=2)])
+def test_wide_per_sample_is_as_exact_as_launches_per_chunk(over):
+    """The persistent kernel's parameters after 500 steps are no further from the oracle's (64 bits)
+    than those of the launches per chunk, which a recorded epoch takes."""
+    w = I.WORKLOADS[1].scaled(**over)
+    K = w.replicas
+    X, y = I.train_set(w, K * 500)
+    th0 = I.init_params(w)
+    xd, yd = dev(X), dev(y)
+    net = make_net(w, th0)
+    assert "psgd_persistent" in kernels_of_an_epoch(net, X, y)
+    ids = [0, K - 1]
+    got = [net.get_params(k) for k in ids]
+    net.set_params(-2, th0)
+    g = torch.cuda.CUDAGraph()
+    torch.cuda.synchronize()
+    with torch.cuda.graph(g):
+        net.train_epoch(xd, yd)
+    g.replay()
+    torch.cuda.synchronize()
+    launches = [net.get_params(k) for k in ids]
+    net.close()
+    ref = oracle_replicas(O.Oracle.from_workload(w), np.tile(th0.astype(np.float64), (2, 1)), ids, X, y)
+
+    def off(p):
+        return float(np.linalg.norm(np.stack(p) - ref) / np.linalg.norm(ref))
+    log(f"persistent {off(got):.2e}, launches per chunk {off(launches):.2e}")
+    assert off(got) <= off(launches)
+
+
 def test_wide_per_sample_late_tiles(monkeypatch):
     """Half of the tile workgroups start late: the sequential workgroup waits for every tile."""
     monkeypatch.setenv("PNN_TEST_TILE_DELAY", "2000")
