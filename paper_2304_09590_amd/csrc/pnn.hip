@@ -9,9 +9,11 @@
 // Training plans:
 //  * per-sample SGD of a one-hidden-layer fp32 network (B = 1, L = 2, hidden <= 1024,
 //    outputs <= 16): hidden <= 384, one persistent launch per epoch and group of CNs
-//    (psgd_persistent_kernel); wider, the chunked plan -- Gram matrices of each chunk of T
-//    samples, then per chunk P = W1 x_t (GEMM), the T sequential steps (psgd_chunk_kernel), and
-//    the rank-T update of W1 (GEMM).
+//    (psgd_persistent_kernel; above 128 where psgd_min_rows has it faster); otherwise the chunked
+//    plan -- Gram matrices of each chunk of T samples, then per chunk P = W1 x_t (GEMM), the T
+//    sequential steps (psgd_chunk_kernel), and the rank-T update of W1 (GEMM).
+//  * batches of at most 64 rows, one hidden layer of <= 512: one persistent launch per epoch and
+//    group of CNs (mbp_kernel) where mbp_faster has it faster.
 //  * everything else: mini-batch plan -- per batch step, forward GEMMs with fused bias and
 //    activation, output layer with fused output error, hidden errors (GEMM with fused
 //    phi'), and weight-gradient GEMMs with the SGD update (and bias update) fused into the
@@ -789,6 +791,19 @@ size_t psgd_gram_elems(const pnn_net* n, int64_t nmax) {
     return (size_t)n->cfg.replicas * std::max(per, chunk);
 }
 
+// The Gram products z = CN * chunks + chunk, in launches of at most 65,535, the grid's limit.  (Chunks
+// of 128 steps, of nets whose inputs are too wide for the persistent kernel, in one: their tiles
+// take no first product.)
+pnn_status gram_products(pnn_net* n, hipStream_t s, GemmArgs& g, int64_t total) {
+    const int64_t most = g.M < 128 ? 65535 : total;
+    for (int64_t z0 = 0; z0 < total; z0 += most) {
+        g.z0 = (int)z0;
+        const int Z = (int)std::min<int64_t>(most, total - z0);
+        TRY((run_gemm<false, float, float, true, true, EPI_STORE, float>(n, s, g, Z, "psgd_gram")));
+    }
+    return PNN_OK;
+}
+
 // after a persistent launch: its abort flag is read by the next call that consumes the CNs
 pnn_status note_persistent_launch(pnn_net* n, hipStream_t s) {
     if (!n->abort_ev) HIP_TRY(n, hipEventCreateWithFlags(&n->abort_ev, hipEventDisableTiming));
@@ -805,15 +820,6 @@ pnn_status psgd_persistent_epoch(pnn_net* n, const float* X, const int32_t* Y, i
     const int GS = psgd_gs(PT);  // padded Gram row stride (the kernel's LDS layout)
     TRY(grow(n, s, &n->gram, &n->gram_elems, psgd_gram_elems(n, nmax)));
     TRY(grow(n, s, &n->gramx, &n->gramx_elems, (size_t)K * std::max(nch - 1, 1) * PT * GS));
-    // (products z = CN * chunks + chunk, in launches of at most 65,535, the grid's limit)
-    auto gram_products = [&](GemmArgs& g, int64_t total) -> pnn_status {
-        for (int64_t z0 = 0; z0 < total; z0 += 65535) {
-            g.z0 = (int)z0;
-            const int Z = (int)std::min<int64_t>(65535, total - z0);
-            TRY((run_gemm<false, float, float, true, true, EPI_STORE, float>(n, s, g, Z, "psgd_gram")));
-        }
-        return PNN_OK;
-    };
     {
         // G_c[t][s] = x_t . x_s within every chunk
         GemmArgs g = gemm_base(n, PT, PT, In, N, 0, PT, 3);
@@ -821,7 +827,7 @@ pnn_status psgd_persistent_epoch(pnn_net* n, const float* X, const int32_t* Y, i
         g.b = opnd(X, 0, In, 1);
         g.zdiv = nch; g.r0_step = PT;
         g.c = n->gram; g.c_z = (int64_t)PT * GS; g.c_ld = GS;
-        TRY(gram_products(g, (int64_t)K * nch));
+        TRY(gram_products(n, s, g, (int64_t)K * nch));
     }
     if (nch > 1) {
         // GX_c[t][s] = x_t . x_s, t in chunk c, s in chunk c-1 (always full), c >= 1
@@ -830,7 +836,7 @@ pnn_status psgd_persistent_epoch(pnn_net* n, const float* X, const int32_t* Y, i
         g.b = opnd(X, 0, In, 1, -PT);
         g.zdiv = nch - 1; g.r0_step = PT;
         g.c = n->gramx; g.c_z = (int64_t)PT * GS; g.c_ld = GS;
-        TRY(gram_products(g, (int64_t)K * (nch - 1)));
+        TRY(gram_products(n, s, g, (int64_t)K * (nch - 1)));
     }
     {
         // (the abort slot flags[3K] is sticky: a launch after an abort ends at once)
@@ -900,6 +906,7 @@ const void* mbp_fn(bool bf16, int rt, int mt) { return bf16 ? mbp_fn_of<true>(rt
 // Above 32 rows three launches at most (784-256-10, K = 128 129 / 113).
 bool mbp_faster(bool bf16, int B, int rt, int groups, int H, int In, int K) {
     if (groups == 1 || H <= 16 || (!bf16 && B <= 32)) return true;
+    if (B <= 32 && K > 65535) return true;  // (the grid's limit in the launches per layer)
     if (B > 32 && groups > 3) return false;
     const double in = In / 784.0, b = B / (B <= 32 ? 32.0 : 64.0), k = K / 100.0, kh = (double)K * H / 1e4;
     const double khin = 1e-2 * kh * In, khb = 1e-2 * kh * B, hb = H / 512.0 * b, rows = 1e-6 * B * In;
@@ -982,7 +989,7 @@ pnn_status psgd_epoch(pnn_net* n, const float* X, const int32_t* Y, int64_t N, h
         g.b = opnd(X, 0, In, 1);
         g.zdiv = nch; g.r0_step = T;
         g.c = n->gram; g.c_z = (int64_t)T * T; g.c_ld = T;
-        TRY((run_gemm<false, float, float, true, true, EPI_STORE, float>(n, s, g, K * nch, "psgd_gram")));
+        TRY(gram_products(n, s, g, (int64_t)K * nch));
     }
     auto run_p = [&](int c) -> pnn_status {
         GemmArgs g = gemm_base(n, T, H, In, N, (int64_t)c * T, T, 1);
@@ -1224,7 +1231,7 @@ pnn_status pnn_init(const pnn_config* cfg, const float* theta0_host, void* hip_s
         // tiles, whose tiles do twice the work per chunk; 1.5 to 1.9 measured with 784-128-10
         // nets, growing with the CNs in flight).  Above 128 neurons a chunk has half the steps and a
         // step takes the live wave longer, so the tiles' work hides behind it: 1.2 up to 256
-        // neurons, 1.1 above (us a step, 16-row / 32-row tiles / launches per chunk: 784-256-10,
+        // neurons, 1.1 above (us a step with act_fast, 16-row / 32-row tiles / launches per chunk: 784-256-10,
         // K = 20 2.06 / 1.27 / 11.0, K = 64 4.97 / 3.38 / 11.2, K = 256 18.4 / 12.0 / 14.9;
         // 784-384-10, K = 64 8.45 / 5.22 / 13.6, K = 256 31.5 / 18.4 / 21.3; where both take one
         // launch 1.14 / 1.14 and 1.42 / 1.40).
@@ -1250,7 +1257,7 @@ pnn_status pnn_init(const pnn_config* cfg, const float* theta0_host, void* hip_s
         const void* fn = persistent_fn(n);
         int per_cu = 0;
         // (above 128 neurons up to 256 CNs, and where slices of some length are the faster for it:
-        // psgd_min_rows; us a step of long slices, this kernel / launches per chunk: 784-136-10, K = 512
+        // psgd_min_rows; us a step of long slices, sigmoids, this kernel / launches per chunk: 784-136-10, K = 512
         // 19.6 / 16.2; 784-384-10, K = 512 43.3 / 43.2, K = 1,024 118 / 91)
         bool fits = H <= PSGD_MAX_H && (H <= 128 || K <= 256) && In <= 4 * MAX_IB * 16 && kg >= 1;
         if (fits && H > 128) {
@@ -1318,7 +1325,8 @@ pnn_status pnn_init(const pnn_config* cfg, const float* theta0_host, void* hip_s
             // tile workgroups of 16 neurons (rt = 1) or 32 (rt = 2); the CNs in groups whose tiles
             // fit the CUs, one launch each; the one with the least estimated time (launches x the
             // relative time of a batch step: 1 with 16-neuron tiles, with 32 1.45, or 1.7 in batches
-            // of more than 32 rows, as measured with 784-256-10 and 784-512-10 nets).
+            // of more than 32 rows, whose instances spill, as measured with 784-256-10 and 784-512-10
+            // nets).
             // Where several launches lose to the launches per layer: mbp_faster.
             const int mt = mbp_row_tiles(B);
             int rt = 0, kg = 0;

@@ -110,6 +110,22 @@ def test_wide_per_sample_short_slices(over, rows, persistent):
     net.close()
 
 
+def test_wide_per_sample_of_many_chunks():
+    """More Gram products than a launch can take (65,535), in the launches per chunk."""
+    w = I.WORKLOADS[1].scaled(sizes=(8, 384, 10), acts=(I.TANH, I.SOFTMAX), loss=I.LOSS_XENT, lr=0.005, replicas=128)
+    K = w.replicas
+    X, y = I.random_batch(8, 10, K * (32 * 512 + 5), 5)
+    th0 = I.init_params(w)
+    net = make_net(w, th0)
+    assert "psgd_chunk" in kernels_of_an_epoch(net, X, y)
+    ids = [0, 126, 127]
+    ref = oracle_replicas(O.Oracle.from_workload(w), np.tile(th0.astype(np.float64), (len(ids), 1)), ids, X, y)
+    for i, k in enumerate(ids):
+        assert_close(w.sizes, net.get_params(k), ref[i], EPOCH_TOL, f"replica {k}")
+        assert_trained(w, net.get_params(k), ref[i], th0, f"replica {k}")
+    net.close()
+
+
 def first_step_w2(H, act2, b1, b2):
     """W2 after an epoch from W2 = 0 with eta = 1 and the cross-entropy error, in which only the first
     row counts: -(x2 - e) a1^T of the activations of the biases themselves.  The first row is zero; the
