@@ -885,11 +885,11 @@ __global__ __launch_bounds__(256) void gemm_kw_kernel(GemmArgs g) {
 // (16 RT) x (16 RT) tiles, the eight waves of a workgroup split the contraction (fp32: wave w takes
 // the 16-deep blocks w, w + 8, ... on v_mfma_f32_16x16x4_f32; bf16: the 32-deep ones on
 // v_mfma_f32_16x16x32_bf16), fragments straight from global memory in the matrix instruction's
-// layout through buffer descriptors (rows past the tile and steps past K read zero), KS_PD steps
+// layout through buffer descriptors (rows past the tile and steps past K read zero), PD blocks
 // ahead.  The partial tiles meet in LDS and are added in pairs, with bias and activation.
 // Bound: latency -- the 64 x 64 tiles walk 49 k-tiles of a 784-long contraction one after another
 // on a handful of CUs, here a wave has 7 steps, all in flight at once or nearly.
-// Inference of 16 rows, 784 -> 128: 30 -> 7 us.  See ks_tile (pnn.hip) for the rule.
+// Inference of 16 rows, 784 -> 128: 30 -> 8 us.  See ks_tile (pnn.hip) for the rule.
 constexpr int KS_WAVES = 8, KS_THREADS = 64 * KS_WAVES;
 
 template <bool BF, typename TA, typename TO, int RT>
@@ -2186,7 +2186,7 @@ struct RowArgs {
 // (row, output): activation, then the output error, or argmax, cost and count by reductions over
 // the 16 lanes of a row.
 // Bound: the read of the hidden activations.  (One wavefront per row, each lane adding up to 16
-// outputs and reducing every one over the wave, took 79 us for 8,192 rows of 1,024, 0.4 TB/s.)
+// outputs and reducing every one over the wave, took 80 us for 8,192 rows of 1,024; this one 14.)
 template <typename TX, typename TW, typename TD, bool TRAIN>
 __global__ __launch_bounds__(256) void out_layer_kernel(RowArgs a) {
     __shared__ float part[4][16][17];
@@ -2437,8 +2437,8 @@ __global__ __launch_bounds__(256) void out_err_kernel(OutErrArgs a) {
 //   rows of an instruction being 4 g + r).
 // At the end W -= lr / B_t dW (master; the bf16 shadow refreshed) and, in the first workgroup of a
 // CN, b -= lr / B_t sum_r delta.  Bound: latency and the pass over the activations.  784-200-104-10,
-// K = 6, B = 100 (a width that is no multiple of 16, where tail_kernel does not apply): 95 us a step
-// in one thread per weight or row and a wavefront per row -> 19 us with out_layer_kernel.
+// K = 6, B = 100 (a width that is no multiple of 16, where tail_kernel does not apply): 100 us a step
+// in one thread per weight or row and a wavefront per row -> 20 us with out_layer_kernel.
 struct LastArgs {
     const void* delta;  // output errors [z][rows][O] (TH)
     int64_t dn_z;
@@ -3156,8 +3156,8 @@ typedef __attribute__((address_space(3))) void lds_void;
 // 1 KiB pieces piece0, piece0 + stride, ...; completion is tracked by the wave's vmcnt.
 __device__ inline void wave_copy_to_lds(const void* src, float* dst_lds, int bytes, int piece0, int stride, int lane) {
     // (the LDS address, the same in every lane, is formed here, opaque to the compiler, which would
-    // keep the address of every piece of every copy in scalar registers all along a kernel, and
-    // spill 17 of them: 784-128-10, K = 4, per-sample, 8.15 -> 8.03 ms a pass)
+    // keep the address of every piece of every copy in scalar registers all along a kernel:
+    // 222 instead of 205 of them spilled, 784-128-10, K = 4, per-sample, 8.15 -> 8.03 ms a pass)
     unsigned dst = (unsigned)(size_t)(lds_void*)dst_lds;
     asm volatile("" : "+v"(dst));
     dst = __builtin_amdgcn_readfirstlane(dst);
@@ -3456,7 +3456,7 @@ __device__ inline void lds_publish(int* f, int v) {
 // The sequential workgroup of one CN (per-sample SGD, one persistent launch per epoch).
 //
 // Notation: steps are numbered over the CN's slice (global step r); chunk c holds steps
-// [cT, cT + T), block B holds steps [BS B, BS B + BS) (BS = 8: eight blocks per chunk).  With W1^(c)
+// [cT, cT + T), block B holds steps [BS B, BS B + BS) (BS = 8: T / 8 blocks per chunk).  With W1^(c)
 // the first-layer weights before chunk c, the first-layer input sum of step r in chunk c is
 //   z1_r = Q_c[r] + b1_r - eta * sum_{s in [T(c-1), r)} d1_s (x_s . x_r)
 // where Q_c[r] = W1^(c-1) x_r is published by the tile workgroups.  The dot products come
@@ -3470,8 +3470,8 @@ __device__ inline void lds_publish(int* f, int v) {
 //   s = r-5 .. r-1:     the live wave, with its own fresh errors (NLIVE = 5 terms).
 //
 // Waves (256 threads), each in its own loop, coordinated through counters in LDS:
-//   wave 0, live:  the steps.  Lane l owns hidden neurons l and l + 64 (NH = 2) or l
-//                  (NH = 1): their b1 and W2 columns stay in registers.
+//   wave 0, live:  the steps.  Lane l owns the NH (1 to 6) hidden neurons l, l + 64, ...:
+//                  their b1 and W2 columns stay in registers.
 //   wave 1:        the window corrections, one row ahead of the live wave.
 //   waves 2, 3:    the folds, each for half of the neurons.  A wave keeps the sums
 //                  sum_s d1_s (x_s . x_t) of the current chunk's rows (accC) and of the next
@@ -3489,8 +3489,8 @@ __device__ inline void lds_publish(int* f, int v) {
 // and the fold waves' accumulators grow as HW T, and so does the matrix work of a fold, so twice
 // the neurons with half the steps cost the same of each; a chunk of 32 steps still takes the live
 // wave far longer (24 us) than the tiles need for their next Q.  Bound: the live wave's chain of
-// dependent steps, 0.52 us a step for 128 neurons, 0.85 us for 256 (0.74 with act_fast, which is
-// less exact than the launches per chunk are).  784-256-10, K = 4, 8,000 rows: 21.5 ms in
+// dependent steps, 0.53 us a step for 128 neurons, 0.85 us for 256 and 1.13 us for 384 (0.74 and 1.0
+// with act_fast, which is less exact than the launches per chunk are).  784-256-10, K = 4, 8,000 rows: 21.5 ms in
 // psgd_chunk_kernel launches (9.9 us a step) -> 1.92 ms.
 // Counters (LDS): d1done (steps whose d1 is in hist), cdone (rows whose cpre is ready),
 // rdy (per folding wave: leading blocks whose rows of Pl are final), gready (chunks whose
@@ -4130,8 +4130,12 @@ __global__ __launch_bounds__(256) void psgd_persistent_kernel(PsgdPArgs a) {
 // of a CN (a store and a load through the memory-side cache, 1.5 us or more), the weight update --
 // of which the fp32 matrix instructions take 2.8 us (B = 32) or 5.5 us (B = 64).  Eight waves, two
 // per SIMD, so that one wave's LDS and memory latency covers the other's matrix instructions.
-// 784-256-10, us a step: K = 16, B = 32: 11.0 (four waves, 64-bit tagged shares polled by every
-// thread) -> 7.0; K = 10, B = 50: 63 in launches per layer -> 12.6; in bf16, 35 -> 9.5.
+// 784-256-10, us a step: K = 16, B = 32: 11.3 (four waves, 64-bit tagged shares polled by every
+// thread) -> 7.5; K = 10, B = 50: 62 in launches per layer -> 12.6; in bf16, 34 -> 9.9.
+// Registers: a wave holds seven input blocks of W1 and of every row tile, so the instances of four row
+// tiles use all 256 and spill -- 16-neuron tiles 15 registers (fp32; 48 bytes a lane) and 13 (bf16;
+// 56 bytes), 32-neuron tiles 110 and 160 (332 and 348 bytes); those of two row tiles spill none.
+// What 32-neuron tiles cost in the choice between the two (pnn_init) includes those spills.
 //
 // Tile workgroup (k, rb) owns, for CN k, the hidden neurons j in [16 RT rb, 16 RT (rb + 1)):
 // their rows of W1 in registers (laid out as in psgd_tile), their biases b1 and their
@@ -4387,8 +4391,9 @@ __global__ __launch_bounds__(MBP_THREADS) void mbp_kernel(MbpArgs a) {
             // them: every tile of the chip polling from the start kept the memory system busy
             // with 5 MB a round, and the shares arrived after 3.5 us.  So the first read waits,
             // longer with the larger batch, whose tiles reach this point further apart
-            // (784-256-10, per step: K = 16, B = 32: 10.8 us without the sleep, 7.4 with 16, 7.9
-            // with 38; K = 10, B = 50: 16.0 without, 15.0 with 16, 13.9 with 38).
+            // (784-256-10, us a step without the sleep / with 16 / with 36: K = 16, B = 32
+            // 10.6 / 7.5 / 8.0; K = 10, B = 50 14.6 / 13.4 / 12.6, in bf16 13.4 / 11.1 / 9.9; a CN of a
+            // single tile, 16 neurons, K = 100, B = 32, has nobody to wait for: 9.5 / 9.8).
             if (wave < nrb) __builtin_amdgcn_s_sleep(MT <= 2 ? 16 : 36);
             while (good && wave < nrb) {
                 uint4 v[NQ][MT];  // (np <= 64 MT)
@@ -4466,8 +4471,7 @@ __global__ __launch_bounds__(MBP_THREADS) void mbp_kernel(MbpArgs a) {
         //    (row tile, sub-tile) per wave (lane: rows 16 mt + 4 g + i, neuron l16); meanwhile the
         //    last waves form W2's gradient, dW2 = delta2^T a1 over the batch (lane: outputs 4 g + i,
         //    neuron l16; one sub-tile each), and update b2.  (Behind the barrier, beside the weight
-        //    update, these held the whole workgroup back at the next step: 784-256-10, B = 50,
-        //    13.5 -> 10.6 us a step.)  Rows past the batch are zero in delta2, a1 and d1.
+        //    update, these held the whole workgroup back at the next step.)  Rows past the batch are zero in delta2, a1 and d1.
 #pragma unroll
         for (int e0 = 0; e0 < MT * RT; e0 += MBP_WAVES) {
             const int e = e0 + wave, mt = e / RT, r = e - mt * RT;
