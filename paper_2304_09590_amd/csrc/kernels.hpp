@@ -2190,7 +2190,8 @@ struct RowArgs {
 template <typename TX, typename TW, typename TD, bool TRAIN>
 __global__ __launch_bounds__(256) void out_layer_kernel(RowArgs a) {
     __shared__ float part[4][16][17];
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, l16 = lane & 15, g = lane >> 4;
+    const int tid = threadIdx.x, lane = tid & 63, l16 = lane & 15, g = lane >> 4;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int row0 = blockIdx.x * 16, zi = blockIdx.z;
     const int64_t v = shard_len(a.n_total, a.k_rep, zi) - a.r0;
     const int valid = (int)(v < 0 ? 0 : v > a.step_rows ? a.step_rows : v);  // (the rows of this step or chunk)
@@ -2224,6 +2225,7 @@ __global__ __launch_bounds__(256) void out_layer_kernel(RowArgs a) {
             for (int p = 0; p < PF; ++p) load(h0 + 64 * p, xv[p], wv[p]);
 #pragma unroll
             for (int p = 0; p < PF; ++p) {
+                if (h0 + 64 * p >= a.H) break;  // (the same for the whole wave)
                 acc[p][0] = __builtin_amdgcn_mfma_f32_16x16x4f32(xv[p].x, wv[p].x, acc[p][0], 0, 0, 0);
                 acc[p][1] = __builtin_amdgcn_mfma_f32_16x16x4f32(xv[p].y, wv[p].y, acc[p][1], 0, 0, 0);
                 acc[p][2] = __builtin_amdgcn_mfma_f32_16x16x4f32(xv[p].z, wv[p].z, acc[p][2], 0, 0, 0);

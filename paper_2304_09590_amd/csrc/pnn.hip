@@ -241,8 +241,9 @@ pnn_status dev_alloc(pnn_net* n, T** p, size_t elems) {
     return PNN_OK;
 }
 
-// is the stream recording a graph?
+// is the stream recording a graph?  (The null stream cannot.)
 bool capturing(hipStream_t s) {
+    if (!s) return false;
     hipStreamCaptureStatus st = hipStreamCaptureStatusNone;
     if (hipStreamIsCapturing(s, &st) != hipSuccess) {
         (void)hipGetLastError();
@@ -1093,7 +1094,7 @@ bool aligned16(const void* p) { return ((uintptr_t)p & 15) == 0; }
 // (Not while the stream `s` records a graph, which allows neither the wait nor the copy: the
 // flag then stays for the next call outside it.)
 pnn_status check_abort(pnn_net* n, bool wait, hipStream_t s) {
-    if (!n->abort_pending || (s && capturing(s))) return PNN_OK;
+    if (!n->abort_pending || capturing(s)) return PNN_OK;
     if (!wait) {
         const hipError_t q = hipEventQuery(n->abort_ev);
         if (q == hipErrorNotReady) return PNN_OK;
