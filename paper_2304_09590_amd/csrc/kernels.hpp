@@ -2203,10 +2203,6 @@ __global__ __launch_bounds__(256) void out_layer_kernel(RowArgs a) {
         const TW* W = (const TW*)a.w + (size_t)zi * a.w_z + (size_t)min(l16, a.O - 1) * a.H;
         constexpr int PF = 4;  // blocks in flight; every instruction of a block has a chain of sums of its own
         f4 acc[PF][4];
-#pragma unroll
-        for (int p = 0; p < PF; ++p)
-#pragma unroll
-            for (int q = 0; q < 4; ++q) acc[p][q] = f4{0.f, 0.f, 0.f, 0.f};
         // a block of 16 along H: this lane's four values of the row and of the output's weights
         // (past H: the row's first values against zero weights)
         auto load = [&](int h0, float4& xv, float4& wv) {
@@ -2219,19 +2215,28 @@ __global__ __launch_bounds__(256) void out_layer_kernel(RowArgs a) {
             if constexpr (sizeof(TW) == 2 && sizeof(TX) == 4)  // bf16 operand
                 xv = make_float4(bf2f(f2bf(xv.x)), bf2f(f2bf(xv.y)), bf2f(f2bf(xv.z)), bf2f(f2bf(xv.w)));
         };
-        for (int h0 = wave * 16; h0 < a.H; h0 += 64 * PF) {
+        // (the first blocks start their chains: no clearing of sixteen accumulators beforehand)
+        auto blocks = [&](int h0, auto first) {
             float4 xv[PF], wv[PF];
 #pragma unroll
             for (int p = 0; p < PF; ++p) load(h0 + 64 * p, xv[p], wv[p]);
 #pragma unroll
             for (int p = 0; p < PF; ++p) {
-                if (h0 + 64 * p >= a.H) break;  // (the same for the whole wave)
-                acc[p][0] = __builtin_amdgcn_mfma_f32_16x16x4f32(xv[p].x, wv[p].x, acc[p][0], 0, 0, 0);
-                acc[p][1] = __builtin_amdgcn_mfma_f32_16x16x4f32(xv[p].y, wv[p].y, acc[p][1], 0, 0, 0);
-                acc[p][2] = __builtin_amdgcn_mfma_f32_16x16x4f32(xv[p].z, wv[p].z, acc[p][2], 0, 0, 0);
-                acc[p][3] = __builtin_amdgcn_mfma_f32_16x16x4f32(xv[p].w, wv[p].w, acc[p][3], 0, 0, 0);
+                const f4 zero = {0.f, 0.f, 0.f, 0.f};
+                if (h0 + 64 * p >= a.H) {  // (the same for the whole wave)
+                    if constexpr (!first) break;
+#pragma unroll
+                    for (int q = 0; q < 4; ++q) acc[p][q] = zero;
+                    continue;
+                }
+                acc[p][0] = __builtin_amdgcn_mfma_f32_16x16x4f32(xv[p].x, wv[p].x, first ? zero : acc[p][0], 0, 0, 0);
+                acc[p][1] = __builtin_amdgcn_mfma_f32_16x16x4f32(xv[p].y, wv[p].y, first ? zero : acc[p][1], 0, 0, 0);
+                acc[p][2] = __builtin_amdgcn_mfma_f32_16x16x4f32(xv[p].z, wv[p].z, first ? zero : acc[p][2], 0, 0, 0);
+                acc[p][3] = __builtin_amdgcn_mfma_f32_16x16x4f32(xv[p].w, wv[p].w, first ? zero : acc[p][3], 0, 0, 0);
             }
-        }
+        };
+        blocks(wave * 16, std::true_type{});
+        for (int h0 = wave * 16 + 64 * PF; h0 < a.H; h0 += 64 * PF) blocks(h0, std::false_type{});
 #pragma unroll
         for (int i = 0; i < 4; ++i) {
             float s[PF];
